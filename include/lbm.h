@@ -201,6 +201,20 @@ lbm_status lbm_set_stream(lbm_lattice* h, void* stream);
  * affected. */
 lbm_status lbm_step(lbm_lattice* h, int64_t nsteps);
 
+/* lbm_step with a workspace: the same steps, states and residuals, bit for
+ * bit.  With at least lbm_step_workspace() bytes of device memory of the
+ * lattice's device in `ws` (256-byte aligned, free to use until the stream has
+ * passed the call; its contents are lost and nothing of the lattice is kept in
+ * it) runs of steps between residual checks take several steps per launch,
+ * reading one of the two buffers and writing the other.  With a NULL or
+ * smaller workspace it is lbm_step. */
+lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size_t ws_bytes);
+
+/* Workspace bytes with which lbm_step_ws(h, nsteps, ...) runs faster than
+ * lbm_step; 0 where it would not use one (large lattices, moving walls or open
+ * faces, few steps, a lattice in a batch, a stream that is being captured). */
+lbm_status lbm_step_workspace(const lbm_lattice* h, int64_t nsteps, size_t* bytes);
+
 /* Current time t (completed steps).  Host-only, no synchronization. */
 lbm_status lbm_time(const lbm_lattice* h, int64_t* t);
 

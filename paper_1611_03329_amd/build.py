@@ -4,15 +4,16 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-SRC = os.path.join(PKG, "csrc", "lbm_capi.hip")
+SRCS = [os.path.join(PKG, "csrc", f) for f in ("lbm_capi.hip", "lbm_multi.hip")]
 LIB = os.path.join(PKG, "liblbm.so")
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
-    f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
+    f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
     # fused multiply-adds only where one source expression has the form a * b + c:
     # the rounding of every step is then the same in every kernel variant
     # (check modes, batch or single lattice), whatever else the compiler sees
@@ -32,11 +33,21 @@ def hipcc() -> str:
 
 
 def build(extra_flags=(), verbose: bool = False) -> str:
+    """Compiles the sources side by side and links the library."""
     tmp = LIB + ".tmp"
-    cmd = [hipcc(), *HIPCC_FLAGS, *extra_flags, SRC, "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    with tempfile.TemporaryDirectory() as work:
+        objs, jobs = [], []
+        for src in SRCS:
+            obj = os.path.join(work, os.path.basename(src) + ".o")
+            cmd = [hipcc(), *HIPCC_FLAGS, *extra_flags, "-c", src, "-o", obj]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            objs.append(obj)
+            jobs.append((cmd, subprocess.Popen(cmd)))
+        failed = [(job.returncode, cmd) for cmd, job in jobs if job.wait() != 0]
+        if failed:
+            raise subprocess.CalledProcessError(*failed[0])
+        subprocess.run([hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp], check=True)
     os.replace(tmp, LIB)
     return LIB
 

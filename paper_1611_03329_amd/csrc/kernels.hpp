@@ -711,7 +711,7 @@ __device__ __forceinline__ void step_block(const KParams<C>& kp, const S& state,
 
 // First stage of the two-stage reduction of per-block partials: block b folds
 // partials [b*blockDim, (b+1)*blockDim) into out[b] (sums; max for maxmask bits).
-__global__ void __launch_bounds__(kMaxBlock) k_fold_partials(const double* __restrict__ in, int count,
+static __global__ void __launch_bounds__(kMaxBlock) k_fold_partials(const double* __restrict__ in, int count,
                                                              unsigned maxmask, double* __restrict__ out) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
@@ -752,7 +752,7 @@ __device__ __forceinline__ void finish_residual(const double (&v)[5], double* __
 // Second stage for a compare step: folds the first-stage partials and forms the
 // residual.  res[0] = r, res[1] = unstable (0/1), res[2..6] = the five totals;
 // res[7] (sticky) is set when unstable.
-__global__ void __launch_bounds__(kMaxBlock) k_residual_final(const double* __restrict__ part, int count,
+static __global__ void __launch_bounds__(kMaxBlock) k_residual_final(const double* __restrict__ part, int count,
                                                               double* __restrict__ res) {
   double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   for (int b = threadIdx.x; b < count; b += blockDim.x) {
@@ -865,7 +865,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_totals(const KParams<C> kp, const
 }
 
 // Second stage for the totals: folds the first-stage partials (two sums).
-__global__ void __launch_bounds__(kMaxBlock) k_sum_final(const double* __restrict__ part, int count,
+static __global__ void __launch_bounds__(kMaxBlock) k_sum_final(const double* __restrict__ part, int count,
                                                          double* __restrict__ out) {
   double v[2] = {0.0, 0.0};
   for (int b = threadIdx.x; b < count; b += blockDim.x) {
@@ -924,7 +924,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_wall_flux(const KParams<C> kp, co
   if (threadIdx.x == 0) part[face * (int)gridDim.x + (int)blockIdx.x] = v[0];
 }
 
-__global__ void __launch_bounds__(64) k_wall_fold(const double* __restrict__ part, int chunks,
+static __global__ void __launch_bounds__(64) k_wall_fold(const double* __restrict__ part, int chunks,
                                                   double* __restrict__ out) {
   if (threadIdx.x != 0) return;
   double s = 0.0;
@@ -959,7 +959,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_get_state(const KParams<C> kp, co
 }
 
 // Sets slot `slot` of a lattice's step count (the slot the next step reads).
-__global__ void __launch_bounds__(64) k_set_clock(uint32_t* clk, int slot, uint32_t value) {
+static __global__ void __launch_bounds__(64) k_set_clock(uint32_t* clk, int slot, uint32_t value) {
   if (threadIdx.x == 0) gbl(clk)[slot] = value;
 }
 

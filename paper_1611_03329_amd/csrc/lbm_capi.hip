@@ -15,6 +15,7 @@
 #include "batch.hpp"
 #include "enthalpy.hpp"
 #include "kernels.hpp"
+#include "multi.hpp"
 
 #include <algorithm>
 #include <mutex>
@@ -50,6 +51,7 @@ struct lbm_lattice {
   lbm_derived d;
   hipStream_t stream = nullptr;
   int device = 0;  // the device current at creation: the lattice's memory lives there
+  BrickShape brick;  // bricks of its two-step passes (lbm_step_ws), if it takes any
   void* buf = nullptr;
   bool owns_buf = false;
   size_t bytes = 0;
@@ -727,6 +729,17 @@ extern "C" lbm_status lbm_create(const lbm_params* p, void* dev_buf, size_t byte
   fill_kparams<float>(p, &d, h->nodes, h->pstride, &h->kf);
   h->even_lds = even_step_lds(p, h->kf, h->nodes);
   h->nxcd = xcd_ranges_for(p, L);
+  if (h->energy) {
+    const int dim[3] = {p->nx, p->ny, p->nz};
+    int ncu = 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && ncu > 0)
+      h->brick = brick_shape_enthalpy(dim, p->precision, ncu);
+  } else if (!(h->kd.moving || h->kd.open_flow || h->kd.open_heat)) {
+    const int dim[3] = {p->nx, p->ny, p->nz};
+    int ncu = 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && ncu > 0)
+      h->brick = brick_shape(dim, p->precision, ncu);
+  }
 
   int iso[6];
   for (int f = 0; f < 6; ++f) {
@@ -882,7 +895,56 @@ static void launch_step(lbm_lattice* h, const KParams<C>& kp, int mode) {
   else launch_step_mode<Lat, S, C, true, false>(h, kp, mode);
 }
 
-extern "C" lbm_status lbm_step(lbm_lattice* h, int64_t nsteps) {
+// ------------------------------------------------------------------ passes of several steps
+// lbm_step_ws advances runs of plain steps several at a time with the kernels
+// of brick.hpp, which read one buffer and write another: the lattice's own
+// populations and a workspace of the same layout that the caller lends for the
+// call.  Passes come in twos, so the state is back in the lattice's buffer when
+// the call has run and nothing of it stays in the workspace.
+
+// Bytes of the population regions, which the layout puts first.
+static size_t population_bytes(const lbm_lattice* h) {
+  return static_cast<size_t>(static_cast<char*>(h->snap) - static_cast<char*>(h->buf));
+}
+
+static StateRegions regions(const lbm_lattice* h, void* base) {
+  auto at = [&](void* region) { return static_cast<char*>(base) + (static_cast<char*>(region) - static_cast<char*>(h->buf)); };
+  return {at(h->mf), at(h->mg), at(h->rs), at(h->r0)};
+}
+
+extern "C" lbm_status lbm_step_workspace(const lbm_lattice* h, int64_t nsteps, size_t* bytes) {
+  if (!h || !bytes) return fail(LBM_ERR_INVALID_ARG, "NULL argument");
+  *bytes = 0;
+  if (nsteps < 4 || h->batch || !h->brick.threads) return LBM_OK;
+  // a captured call would tie the graph to a workspace that is only lent
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (h->stream && hipStreamIsCapturing(h->stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return LBM_OK;
+  }
+  if (cap == hipStreamCaptureStatusNone) *bytes = population_bytes(h);
+  return LBM_OK;
+}
+
+// 2 * passes plain steps of a lattice at parity 0 (passes even).
+static lbm_status step_bricks(lbm_lattice* h, int64_t passes, void* ws) {
+  const StateRegions home = regions(h, h->buf), away = regions(h, ws);
+  const int dim[3] = {h->p.nx, h->p.ny, h->p.nz};
+  for (int64_t k = 0; k < passes; ++k) {
+    // the member table starts with the lattice's kernel parameters
+    launch_brick2(h->q, h->prec, h->dev_member, dim, h->brick, k & 1 ? away : home, k & 1 ? home : away, (uint32_t)h->t,
+                  h->stream);
+    lbm_status ls = launch_check("two-step pass");
+    if (ls != LBM_OK) return ls;
+    h->t += 2;
+  }
+  // the step count drives FP16 rounding only
+  return h->prec == LBM_FP16_STORAGE ? set_clock(h) : LBM_OK;
+}
+
+extern "C" lbm_status lbm_step(lbm_lattice* h, int64_t nsteps) { return lbm_step_ws(h, nsteps, nullptr, 0); }
+
+extern "C" lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size_t ws_bytes) {
   if (!h) return fail(LBM_ERR_INVALID_ARG, "lattice is NULL");
   if (nsteps < 0) return fail(LBM_ERR_INVALID_ARG, "nsteps must be >= 0");
   if (h->batch) return fail(LBM_ERR_INVALID_ARG, "the lattice is in a batch: step the batch");
@@ -892,7 +954,24 @@ extern "C" lbm_status lbm_step(lbm_lattice* h, int64_t nsteps) {
     const EnthalpyConsts<float> e32 = enthalpy_consts<float>(&h->p);
     using S64 = Store<double, double, double>;
     using S32 = Store<float, float, float>;
+    const bool passes = ws && h->brick.threads && ws_bytes >= population_bytes(h);
     for (int64_t s = 0; s < nsteps; ++s) {
+      const int64_t left = nsteps - s;
+      if (passes && h->parity == 0 && left >= 4) {
+        // an even number of passes of about equal length
+        const int64_t n = (left + 2 * h->brick.steps - 1) / (2 * h->brick.steps) * 2;
+        const StateRegions home = regions(h, h->buf), away = regions(h, ws);
+        for (int64_t k = 0; k < n; ++k) {
+          const int steps = (int)(left * (k + 1) / n - left * k / n);
+          const StateRegions &src = k & 1 ? away : home, &dst = k & 1 ? home : away;
+          if (h->prec == LBM_FP64) launch_brick_enthalpy(h->kd, e64, h->brick, steps, src, dst, h->stream);
+          else launch_brick_enthalpy(h->kf, e32, h->brick, steps, src, dst, h->stream);
+          lbm_status ls = launch_check("enthalpy pass");
+          if (ls != LBM_OK) return ls;
+          h->t += steps;
+        }
+        return LBM_OK;
+      }
       const dim3 g(h->nblocks), b(h->block);
       if (h->prec == LBM_FP64) {
         if (h->parity) hipLaunchKernelGGL((k_step_enthalpy<S64, double, true>), g, b, 0, h->stream, h->kd, e64, make_store<S64>(h));
@@ -909,9 +988,22 @@ extern "C" lbm_status lbm_step(lbm_lattice* h, int64_t nsteps) {
     return LBM_OK;
   }
   const int64_t K = h->p.check_interval;
+  const bool bricks = ws && h->brick.threads && ws_bytes >= population_bytes(h);
   for (int64_t s = 0; s < nsteps; ++s) {
     int mode = kModePlain;
     const int64_t t = h->t;
+    if (bricks && h->parity == 0 && (K == 0 || t == 0 || t % K != 0)) {
+      // plain steps ahead: up to the snapshot step before the next check
+      int64_t plain = nsteps - s;
+      if (K > 0) plain = std::min(plain, K - 1 - t % K);
+      if (plain >= 4) {
+        const int64_t passes = plain / 4 * 2;
+        lbm_status ls = step_bricks(h, passes, ws);
+        if (ls != LBM_OK) return ls;
+        s += 2 * passes - 1;
+        continue;
+      }
+    }
     if (K > 0) {
       if ((t + 1) % K == 0) mode = kModeSnapshot;
       else if (t > 0 && t % K == 0 && h->snapshot_valid && h->snapshot_at == t - 1) mode = kModeCompare;

@@ -1,0 +1,206 @@
+// lbm_multi.hip -- launches of the kernels that take several steps per launch.
+#include "multi.hpp"
+
+#include <algorithm>
+
+#include "brick.hpp"
+#include "lbm.h"
+
+namespace lbm {
+
+template <class S>
+static S store_of(const StateRegions& r) {
+  S s;
+  s.mf = static_cast<typename S::MoveF*>(r.mf);
+  s.mg = static_cast<typename S::MoveG*>(r.mg);
+  s.rs = static_cast<typename S::Rest*>(r.rs);
+  s.r0 = static_cast<typename S::MoveF*>(r.r0);
+  return s;
+}
+
+static int cuts(int n, int b) { return (n + b - 1) / b; }
+
+// Local box of brick b with `layers` around it along the axes it does not span.
+static int local_nodes(const int dim[3], const int b[3], int layers) {
+  int e = 1;
+  for (int a = 0; a < 3; ++a) e *= b[a] + (b[a] < dim[a] ? 2 * layers : 0);
+  return e;
+}
+
+// Estimated time (us) of a two-step pass: launch and first touch, then per
+// filling of the CUs (a block's LDS limits how many share one) a fixed part and
+// one that grows with the wavefronts W of step 1 on a CU, and the traffic of
+// all local nodes (rows of x that are no multiple of 8 nodes cost more).  Fitted to sweeps of bricks on 8^3 to 64^3 boxes, which it meets to
+// about 10 %.
+static double brick_pass_us(int prec, int nx, long long blocks, int local, int share, int ncu) {
+  const long long per_cu = (blocks + ncu - 1) / ncu;
+  const long long rounds = (per_cu + share - 1) / share;
+  const double W = (double)std::min<long long>(share, per_cu) * ((local + 63) / 64);
+  const double all = (double)blocks * local / 131072.0;
+  if (prec == LBM_FP64) return 1.2 + rounds * (4.0 + 0.4 * W) + 2.5 * all;
+  const bool rows = nx % 8 == 0;
+  if (rounds > 1 || W > 12.0)
+    return (rows ? 1.0 : 1.2) * (1.5 + rounds * (6.4 + 0.62 * std::max(0.0, W - 12.0)));
+  return 5.5 + 0.2 * W + (rows ? 1.0 : 3.0) * all;
+}
+
+// Bricks of the two-step pass, chosen by that estimate where it is 10 % below
+// two single steps (s0 + s1 nodes each).  Bricks that span x read and write
+// whole rows; others pay 1.2x, with short rows 1.5x.  Measured per step (us),
+// two-step passes against k_step: FP64 8^3 3.7 / 5.0, 16x12x10 3.9 / 5.0, 24^3 5.3 /
+// 6.5, 32^3 5.7 / 8.6, 40^3 8.4 / 12.3, 100x20x20 6.4 / 8.4, but 48^3 12.2 / 11.2 and 64^3
+// 25 / 20 at best; FP32 16x12x10 3.4 / 4.0, 32^3 4.0 / 5.5, 40^3 6.5 / 7.7, but 28^3 4.7 /
+// 5.0, 100x20x20 5.9 / 5.7, 64^3 13.8 / 10.7; FP16 16x12x10 3.7 / 4.3, 32^3 4.1 / 5.2, but
+// 36^3 5.7 / 5.6.  Above the node limits the layers' redundant work costs more
+// than the launches saved, or the estimate no longer tells.
+BrickShape brick_shape(const int dim[3], int prec, int ncu) {
+  const bool fp64 = prec == LBM_FP64, fp16 = prec == LBM_FP16_STORAGE;
+  const long long nodes = (long long)dim[0] * dim[1] * dim[2];
+  BrickShape best;
+  if (nodes > (fp64 ? 90000 : (fp16 ? 40000 : 70000))) return best;
+  const double single = fp64 ? 4.7 + 1.1e-4 * nodes : (fp16 ? 4.0 + 3.5e-5 * nodes : 3.7 + 5.5e-5 * nodes);
+  double least = 0.9 * single;
+  for (int kx = 1; kx <= 16 && (kx == 1 || cuts(dim[0], kx) >= 4); ++kx)
+    for (int by = 1; by <= 8; ++by)
+      for (int bz = 1; bz <= 8; ++bz) {
+        // equal bricks along each axis
+        const int b[3] = {cuts(dim[0], kx), cuts(dim[1], cuts(dim[1], by)), cuts(dim[2], cuts(dim[2], bz))};
+        const int e = local_nodes(dim, b, 1);
+        if (e > 768) continue;
+        const int threads = e <= 256 ? 256 : (e <= 512 ? 512 : 768);
+        const int share = fp64 ? (threads == 256 ? 3 : 1) : (threads == 256 ? 6 : (threads == 512 ? 3 : 2));
+        const long long blocks = (long long)cuts(dim[0], b[0]) * cuts(dim[1], b[1]) * cuts(dim[2], b[2]);
+        double t = 0.5 * brick_pass_us(prec, dim[0], blocks, e, share, ncu);
+        if (b[0] < dim[0]) t *= b[0] >= (fp64 ? 12 : 24) ? 1.2 : 1.5;
+        if (t < least) {
+          least = t;
+          for (int a = 0; a < 3; ++a) best.b[a] = b[a];
+          best.threads = threads;
+          best.steps = 2;
+        }
+      }
+  return best;
+}
+
+// The same for enthalpy lattices, whose node takes a fraction of the work, so
+// that more steps per pass pay: pass = 4.5 + rounds T (c0 + c1 L / 1024), L the
+// local nodes of the blocks that share a CU.  Measured per step against
+// k_step_enthalpy: 400x6x6 FP64 1.5 / 2.9-4.0 us (T = 6), FP32 1.1 / 4.2 (T = 12),
+// 120x16x15 FP64 2.6 / 4.2, FP32 2.2 / 3.9 (T = 3), but FP64 141x38x37 8.3 / 8.1 and
+// 320x53x53 24 / 16.
+BrickShape brick_shape_enthalpy(const int dim[3], int prec, int ncu) {
+  const bool fp64 = prec == LBM_FP64;
+  const long long nodes = (long long)dim[0] * dim[1] * dim[2];
+  BrickShape best;
+  if (nodes > 150000) return best;
+  const double c0 = fp64 ? 0.35 : 0.3, c1 = fp64 ? 0.9 : 0.45;
+  double least = 0.85 * (fp64 ? 3.0 + 2.2e-5 * nodes : 3.2 + 1.3e-5 * nodes);
+  const int edges[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 0};  // 0: the whole axis
+  for (int T : {2, 3, 4, 6, 8, 12})
+    for (int ex : edges)
+      for (int ey : edges)
+        for (int ez : edges) {
+          const int want[3] = {ex, ey, ez};
+          int b[3];
+          bool ok = true;
+          for (int a = 0; a < 3; ++a) {
+            b[a] = want[a] == 0 ? dim[a] : want[a];
+            // a brick that does not span its axis needs T - 1 layers of other nodes
+            ok = ok && (want[a] == 0 || (b[a] < dim[a] && T - 1 <= dim[a]));
+          }
+          if (!ok || b[0] > 1024 || b[1] > 1024 || b[2] > 1024) continue;
+          if ((long long)b[0] * b[1] * b[2] > 1024) continue;
+          const int e = local_nodes(dim, b, T - 1);
+          if (e > 1024) continue;
+          const int threads = e <= 256 ? 256 : (e <= 512 ? 512 : 1024);
+          const int share = (fp64 ? 1 : 2) * (1024 / threads);
+          const long long blocks = (long long)cuts(dim[0], b[0]) * cuts(dim[1], b[1]) * cuts(dim[2], b[2]);
+          const long long per_cu = (blocks + ncu - 1) / ncu;
+          const long long rounds = (per_cu + share - 1) / share;
+          const double local = (double)std::min<long long>(share, per_cu) * e;
+          double t = 4.5 / T + rounds * (c0 + c1 * local / 1024.0);
+          if (b[0] < dim[0] && b[0] < 8) t *= 1.1;  // short rows
+          if (t < least) {
+            least = t;
+            for (int a = 0; a < 3; ++a) best.b[a] = b[a];
+            best.threads = threads;
+            best.steps = T;
+          }
+        }
+  return best;
+}
+
+static BrickGrid brick_grid(const int dim[3], const BrickShape& s, int layers) {
+  BrickGrid g;
+  for (int a = 0; a < 3; ++a) {
+    g.b[a] = s.b[a];
+    g.halo[a] = s.b[a] < dim[a] ? layers : 0;
+    g.e[a] = s.b[a] + 2 * g.halo[a];
+  }
+  g.inv_b0 = 1.0f / (float)g.b[0];
+  g.inv_b01 = 1.0f / (float)(g.b[0] * g.b[1]);
+  g.inv_e0 = 1.0f / (float)g.e[0];
+  g.inv_e01 = 1.0f / (float)(g.e[0] * g.e[1]);
+  return g;
+}
+
+template <class Lat, class S, class C, int NT>
+static void launch_brick2_nt(const void* params, const int dim[3], const BrickShape& s, const StateRegions& src,
+                             const StateRegions& dst, uint32_t now, hipStream_t stream) {
+  const dim3 grid((dim[0] + s.b[0] - 1) / s.b[0], (dim[1] + s.b[1] - 1) / s.b[1], (dim[2] + s.b[2] - 1) / s.b[2]);
+  hipLaunchKernelGGL((k_brick2<Lat, S, C, NT>), grid, dim3(NT), 0, stream, static_cast<const KParams<C>*>(params), store_of<S>(src), store_of<S>(dst),
+                     brick_grid(dim, s, 1), now);
+}
+
+template <class Lat, class S, class C>
+static void launch_brick2_of(const void* params, const int dim[3], const BrickShape& s, const StateRegions& src,
+                             const StateRegions& dst, uint32_t now, hipStream_t stream) {
+  if (s.threads == 256) launch_brick2_nt<Lat, S, C, 256>(params, dim, s, src, dst, now, stream);
+  else if (s.threads == 512) launch_brick2_nt<Lat, S, C, 512>(params, dim, s, src, dst, now, stream);
+  else launch_brick2_nt<Lat, S, C, 768>(params, dim, s, src, dst, now, stream);
+}
+
+void launch_brick2(int q, int prec, const void* params, const int dim[3], const BrickShape& shape,
+                   const StateRegions& src, const StateRegions& dst, uint32_t now, hipStream_t stream) {
+  using S64 = Store<double, double, double>;
+  using S32 = Store<float, float, float>;
+  using S16 = Store<_Float16, float, float>;
+  if (q == 19) {
+    if (prec == LBM_FP64) launch_brick2_of<D3Q19, S64, double>(params, dim, shape, src, dst, now, stream);
+    else if (prec == LBM_FP32) launch_brick2_of<D3Q19, S32, float>(params, dim, shape, src, dst, now, stream);
+    else launch_brick2_of<D3Q19, S16, float>(params, dim, shape, src, dst, now, stream);
+  } else {
+    if (prec == LBM_FP64) launch_brick2_of<D3Q15, S64, double>(params, dim, shape, src, dst, now, stream);
+    else if (prec == LBM_FP32) launch_brick2_of<D3Q15, S32, float>(params, dim, shape, src, dst, now, stream);
+    else launch_brick2_of<D3Q15, S16, float>(params, dim, shape, src, dst, now, stream);
+  }
+}
+
+template <class C, int NT>
+static void launch_brick_enthalpy_nt(const KParams<C>& kp, const EnthalpyConsts<C>& ec, const BrickShape& s, int steps,
+                                     const StateRegions& src, const StateRegions& dst, hipStream_t stream) {
+  using S = Store<C, C, C>;
+  const int dim[3] = {kp.nx, kp.ny, kp.nz};
+  const dim3 grid((dim[0] + s.b[0] - 1) / s.b[0], (dim[1] + s.b[1] - 1) / s.b[1], (dim[2] + s.b[2] - 1) / s.b[2]);
+  hipLaunchKernelGGL((k_brick_enthalpy<S, C, NT>), grid, dim3(NT), 0, stream, kp, ec, store_of<S>(src),
+                     store_of<S>(dst), brick_grid(dim, s, steps - 1), steps);
+}
+
+template <class C>
+static void launch_brick_enthalpy_of(const KParams<C>& kp, const EnthalpyConsts<C>& ec, const BrickShape& s, int steps,
+                                     const StateRegions& src, const StateRegions& dst, hipStream_t stream) {
+  if (s.threads == 256) launch_brick_enthalpy_nt<C, 256>(kp, ec, s, steps, src, dst, stream);
+  else if (s.threads == 512) launch_brick_enthalpy_nt<C, 512>(kp, ec, s, steps, src, dst, stream);
+  else launch_brick_enthalpy_nt<C, 1024>(kp, ec, s, steps, src, dst, stream);
+}
+
+void launch_brick_enthalpy(const KParams<float>& kp, const EnthalpyConsts<float>& ec, const BrickShape& shape,
+                           int steps, const StateRegions& src, const StateRegions& dst, hipStream_t stream) {
+  launch_brick_enthalpy_of(kp, ec, shape, steps, src, dst, stream);
+}
+void launch_brick_enthalpy(const KParams<double>& kp, const EnthalpyConsts<double>& ec, const BrickShape& shape,
+                           int steps, const StateRegions& src, const StateRegions& dst, hipStream_t stream) {
+  launch_brick_enthalpy_of(kp, ec, shape, steps, src, dst, stream);
+}
+
+}  // namespace lbm

@@ -1,0 +1,41 @@
+// multi.hpp -- host entry points of the kernels that take several steps per
+// launch (lbm_multi.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "enthalpy.hpp"
+#include "model.hpp"
+
+namespace lbm {
+
+// Untyped population regions of one state (see Store in kernels.hpp).
+struct StateRegions {
+  void *mf, *mg, *rs, *r0;
+};
+
+// Brick edges a lattice of this shape is cut into (0: it is not).
+struct BrickShape {
+  int b[3] = {0, 0, 0};
+  int threads = 0;
+  int steps = 0;  // most time steps per pass
+};
+
+// prec: lbm_precision; ncu: compute units of the device.
+BrickShape brick_shape(const int dim[3], int prec, int ncu);
+BrickShape brick_shape_enthalpy(const int dim[3], int prec, int ncu);
+
+// `steps` <= shape.steps time steps of an enthalpy lattice.
+void launch_brick_enthalpy(const KParams<float>& kp, const EnthalpyConsts<float>& ec, const BrickShape& shape,
+                           int steps, const StateRegions& src, const StateRegions& dst, hipStream_t stream);
+void launch_brick_enthalpy(const KParams<double>& kp, const EnthalpyConsts<double>& ec, const BrickShape& shape,
+                           int steps, const StateRegions& src, const StateRegions& dst, hipStream_t stream);
+
+// Two time steps src -> dst (natural layout) of a lattice with q = 19 or 15
+// flow populations at step count `now`; params: its KParams in device memory.
+void launch_brick2(int q, int prec, const void* params, const int dim[3], const BrickShape& shape,
+                   const StateRegions& src, const StateRegions& dst, uint32_t now, hipStream_t stream);
+
+}  // namespace lbm

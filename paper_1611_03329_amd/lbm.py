@@ -103,6 +103,8 @@ _lib.lbm_create.argtypes = [_P, _V, ctypes.c_size_t, _V, ctypes.POINTER(_V)]
 _lib.lbm_destroy.argtypes = [_V]
 _lib.lbm_set_stream.argtypes = [_V, _V]
 _lib.lbm_step.argtypes = [_V, ctypes.c_int64]
+_lib.lbm_step_ws.argtypes = [_V, ctypes.c_int64, _V, ctypes.c_size_t]
+_lib.lbm_step_workspace.argtypes = [_V, ctypes.c_int64, ctypes.POINTER(ctypes.c_size_t)]
 _lib.lbm_time.argtypes = [_V, _I64]
 _lib.lbm_derived_params.argtypes = [_V, ctypes.POINTER(Derived)]
 _lib.lbm_fields.argtypes = [_V, _V, _V, _V, _V, _V]
@@ -134,6 +136,7 @@ _lib.lbm_batch_set_span.argtypes = [_V, ctypes.c_int32]
 _lib.lbm_batch_set_class_block.argtypes = [_V, ctypes.c_int32, ctypes.c_int32]
 _lib.lbm_batch_class_block.argtypes = [_V, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
 for _name in ("lbm_required_bytes", "lbm_create", "lbm_destroy", "lbm_set_stream", "lbm_step",
+              "lbm_step_ws", "lbm_step_workspace",
               "lbm_time", "lbm_derived_params", "lbm_fields", "lbm_fields_noalloc", "lbm_nusselt", "lbm_nusselt_start", "lbm_residual",
               "lbm_totals", "lbm_get_state", "lbm_set_state", "lbm_transfer_state", "lbm_enthalpy_fields", "lbm_batch_create", "lbm_batch_destroy",
               "lbm_batch_add", "lbm_batch_remove", "lbm_batch_size", "lbm_batch_member", "lbm_batch_step",
@@ -260,7 +263,29 @@ class Lattice:
 
     # -- stepping
     def step(self, n: int = 1):
-        _check(_lib.lbm_step(self._h, int(n)))
+        """n time steps.  Where several steps per launch pay (lbm_step_workspace)
+        they get a second buffer for the length of the call, from torch's
+        allocator on the lattice's stream; without memory for it the steps run
+        one by one."""
+        n = int(n)
+        need = ctypes.c_size_t()
+        _check(_lib.lbm_step_workspace(self._h, n, ctypes.byref(need)))
+        if need.value:
+            try:
+                # freed when this returns: the allocator hands it out again in the
+                # order of the stream it came from, which is the lattice's
+                if self.stream.cuda_stream == torch.cuda.current_stream(self.device).cuda_stream:
+                    ws = torch.empty(need.value + 256, dtype=torch.uint8, device=self.device)
+                else:
+                    with torch.cuda.stream(self.stream):
+                        ws = torch.empty(need.value + 256, dtype=torch.uint8, device=self.device)
+            except torch.cuda.OutOfMemoryError:
+                ws = None
+            if ws is not None:
+                base = (ws.data_ptr() + 255) // 256 * 256
+                _check(_lib.lbm_step_ws(self._h, n, ctypes.c_void_p(base), ctypes.c_size_t(need.value)))
+                return
+        _check(_lib.lbm_step(self._h, n))
 
     @property
     def time(self) -> int:

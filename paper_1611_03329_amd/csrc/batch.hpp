@@ -131,7 +131,7 @@ constexpr auto step_kernel() {
 }
 
 // Block m folds member m's partials of the last compare step and forms its
-// residual (as k_fold_partials + k_residual_final do for one lattice); the
+// residual (as k_fold does for one lattice); the
 // result goes to the member's own area and to out[m * kPartStride ...].
 template <class S, class C>
 __global__ void __launch_bounds__(kMaxBlock) k_fold_members(const Member<S, C>* __restrict__ mem,

@@ -709,21 +709,19 @@ __device__ __forceinline__ void step_block(const KParams<C>& kp, const S& state,
   }
 }
 
-// First stage of the two-stage reduction of per-block partials: block b folds
-// partials [b*blockDim, (b+1)*blockDim) into out[b] (sums; max for maxmask bits).
-static __global__ void __launch_bounds__(kMaxBlock) k_fold_partials(const double* __restrict__ in, int count,
-                                                             unsigned maxmask, double* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  if (i < count) {
-#pragma unroll
-    for (int j = 0; j < 5; ++j) v[j] = in[(size_t)i * kPartStride + j];
-  }
-  block_reduce<5>(v, maxmask);
+// Whether this block is the last of `total` to get here (thread 0's earlier
+// stores are then visible to the caller from every block).  The last block
+// leaves *count at 0 for the next launch.
+__device__ __forceinline__ bool last_block(uint32_t* count, uint32_t total) {
+  __shared__ int last;
   if (threadIdx.x == 0) {
-#pragma unroll
-    for (int j = 0; j < 5; ++j) out[(size_t)blockIdx.x * kPartStride + j] = v[j];
+    __threadfence();
+    last = __hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == total - 1;
+    if (last) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  __syncthreads();
+  if (last) __threadfence();
+  return last;
 }
 
 // Forms the residual from the folded sums (sum|du|^2, sum|u|^2, sum dtheta^2,
@@ -749,19 +747,48 @@ __device__ __forceinline__ void finish_residual(const double (&v)[5], double* __
   if (bad) res[7] = 1.0;
 }
 
-// Second stage for a compare step: folds the first-stage partials and forms the
-// residual.  res[0] = r, res[1] = unstable (0/1), res[2..6] = the five totals;
-// res[7] (sticky) is set when unstable.
-static __global__ void __launch_bounds__(kMaxBlock) k_residual_final(const double* __restrict__ part, int count,
-                                                              double* __restrict__ res) {
-  double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int b = threadIdx.x; b < count; b += blockDim.x) {
+// Folds the per-block partials of a compare step (RES) or of the totals in two
+// deterministic stages: block b folds partials [b group, (b + 1) group) into
+// part2[b] (sums; entry 4 a max), the last block to finish folds part2 and forms
+// the residual (res[0] = r, res[1] = unstable (0/1), res[2..6] the five totals,
+// res[7] sticky) or the two sums.  The result goes to device memory and to the
+// host's pinned mirror.  One launch and no copy: as two launches and a copy a
+// check of a small lattice took 20 us beside steps of 4-5 us.
+template <bool RES>
+__global__ void __launch_bounds__(kMaxBlock) k_fold(const double* __restrict__ in, int count, int group,
+                                                    double* part2, uint32_t* done, double* res, double* host) {
+  constexpr unsigned maxmask = RES ? 1u << 4 : 0u;
+  constexpr int NV = RES ? 5 : 2;
+  const int i = blockIdx.x * group + threadIdx.x;
+  double v[NV];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] += part[(size_t)b * kPartStride + j];
-    v[4] = pick_max(v[4], part[(size_t)b * kPartStride + 4]);
+  for (int j = 0; j < NV; ++j) v[j] = (int)threadIdx.x < group && i < count ? in[(size_t)i * kPartStride + j] : 0.0;
+  block_reduce<NV>(v, maxmask);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) part2[(size_t)blockIdx.x * kPartStride + j] = v[j];
   }
-  block_reduce<5>(v, 1u << 4);
-  if (threadIdx.x == 0) finish_residual(v, res);
+  if (!last_block(done, gridDim.x)) return;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) v[j] = 0.0;
+  for (int b = threadIdx.x; b < (int)gridDim.x; b += blockDim.x) {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const double w = part2[(size_t)b * kPartStride + j];
+      v[j] = ((maxmask >> j) & 1u) ? pick_max(v[j], w) : v[j] + w;
+    }
+  }
+  block_reduce<NV>(v, maxmask);
+  if (threadIdx.x == 0) {
+    if constexpr (RES) {
+      finish_residual(v, res);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) host[j] = res[j];
+    } else {
+      res[0] = host[0] = v[0];
+      res[1] = host[1] = v[1];
+    }
+  }
 }
 
 // ------------------------------------------------------------------ init
@@ -864,26 +891,12 @@ __global__ void __launch_bounds__(kMaxBlock) k_totals(const KParams<C> kp, const
   }
 }
 
-// Second stage for the totals: folds the first-stage partials (two sums).
-static __global__ void __launch_bounds__(kMaxBlock) k_sum_final(const double* __restrict__ part, int count,
-                                                         double* __restrict__ out) {
-  double v[2] = {0.0, 0.0};
-  for (int b = threadIdx.x; b < count; b += blockDim.x) {
-    v[0] += part[(size_t)b * kPartStride + 0];
-    v[1] += part[(size_t)b * kPartStride + 1];
-  }
-  block_reduce<2>(v, 0u);
-  if (threadIdx.x == 0) {
-    out[0] = v[0];
-    out[1] = v[1];
-  }
-}
-
 // Heat entering through each isothermal face during the last streaming, in
-// two deterministic stages.  k_wall_flux: block (b, f) sums, in FP64, 2 g_k -
-// 2 omega_k sigma T_w over chunk b (of gridDim.x equal chunks) of face f's
-// wall nodes, k the population entering the fluid, into part[f * gridDim.x +
-// b]; k_wall_fold adds each face's chunk sums in order into out[face].  The
+// two deterministic stages: block (b, f) sums, in FP64, 2 g_k - 2 omega_k sigma
+// T_w over chunk b (of gridDim.x equal chunks) of face f's wall nodes, k the
+// population entering the fluid, into part[f * gridDim.x + b]; the last block
+// adds each face's chunk sums in order into out[face] and host[face] (the
+// host's pinned mirror).  The
 // wall term 2 omega_k sigma T_w is taken as the step applies it, in the step's
 // precision: the sum is then exactly the heat the discrete model exchanges
 // with the wall.  (At Ra = 1e6 the flux per node is about 1/700 of a
@@ -891,8 +904,8 @@ static __global__ void __launch_bounds__(kMaxBlock) k_sum_final(const double* __
 // 4e-5.)
 template <class Lat, class S, class C, bool ODD>
 __global__ void __launch_bounds__(kMaxBlock) k_wall_flux(const KParams<C> kp, const S state,
-                                                         const int* __restrict__ isothermal,
-                                                         double* __restrict__ part) {
+                                                         const int* __restrict__ isothermal, double* part,
+                                                         uint32_t* done, double* out, double* host) {
   const int face = blockIdx.y;
   const int a = face >> 1, side = face & 1;
   const int dim[3] = {kp.nx, kp.ny, kp.nz};
@@ -921,15 +934,13 @@ __global__ void __launch_bounds__(kMaxBlock) k_wall_flux(const KParams<C> kp, co
     }
   }
   block_reduce<1>(v, 0u);
-  if (threadIdx.x == 0) part[face * (int)gridDim.x + (int)blockIdx.x] = v[0];
-}
-
-static __global__ void __launch_bounds__(64) k_wall_fold(const double* __restrict__ part, int chunks,
-                                                  double* __restrict__ out) {
-  if (threadIdx.x != 0) return;
+  const int chunks = (int)gridDim.x;
+  if (threadIdx.x == 0) part[face * chunks + (int)blockIdx.x] = v[0];
+  if (!last_block(done, gridDim.x * gridDim.y) || threadIdx.x >= 6) return;
+  const int f = (int)threadIdx.x;
   double s = 0.0;
-  for (int b = 0; b < chunks; ++b) s += part[blockIdx.x * chunks + b];
-  out[blockIdx.x] = s;
+  for (int b = 0; b < chunks; ++b) s += part[f * chunks + b];
+  out[f] = host[f] = s;
 }
 
 // ------------------------------------------------------------------ state I/O

@@ -75,9 +75,10 @@ struct lbm_lattice {
   int nfold = 0;            // entries in part2
   double* res = nullptr;    // [0..7] residual, [8..13] wall flux, [16..17] totals
   uint32_t* clk = nullptr;  // [2] step count by parity (drives FP16 stochastic rounding)
+  uint32_t* done = nullptr; // blocks of a reduction that have finished (0 between launches)
   void* dev_member = nullptr; // the lattice as a one-member table for the step kernel
   int* dev_iso = nullptr;   // [6] isothermal flags
-  double* host_res = nullptr; // pinned mirror of res (32 doubles)
+  double* host_res = nullptr; // pinned mirror of res (32 doubles), written by the kernels
   int parity = 0;
   bool nu_pending = false;  // lbm_nusselt_start enqueued a wall-flux reduction not yet collected
   int64_t t = 0;
@@ -723,6 +724,7 @@ extern "C" lbm_status lbm_create(const lbm_params* p, void* dev_buf, size_t byte
   h->nfold = L.nfold;
   h->res = reinterpret_cast<double*>(base + L.res);
   h->clk = reinterpret_cast<uint32_t*>(base + L.clk);
+  h->done = h->clk + 32;  // in the clock's 256 bytes, on a line of its own
   h->dev_iso = reinterpret_cast<int*>(base + L.iso);
   h->dev_member = base + L.member;
   fill_kparams<double>(p, &d, h->nodes, h->pstride, &h->kd);
@@ -1018,12 +1020,10 @@ extern "C" lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size
       h->snapshot_at = t;
     }
     if (mode == kModeCompare) {
-      hipLaunchKernelGGL(k_fold_partials, dim3(h->nfold), dim3(h->block), 0, h->stream, h->part, h->nblocks,
-                         1u << 4, h->part2);
-      hipLaunchKernelGGL(k_residual_final, dim3(1), dim3(256), 0, h->stream, h->part2, h->nfold, h->res);
+      hipLaunchKernelGGL(k_fold<true>, dim3(h->nfold), dim3(256), 0, h->stream, h->part, h->nblocks, h->block,
+                         h->part2, h->done, h->res, h->host_res);
       ls = launch_check("residual");
       if (ls != LBM_OK) return ls;
-      HIP_TRY(hipMemcpyAsync(h->host_res, h->res, 8 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
       h->last_check = t;
       h->snapshot_valid = false;
     }
@@ -1156,7 +1156,7 @@ extern "C" lbm_status lbm_fields_noalloc(lbm_lattice* h, double* rho, double* ux
 }
 
 // Enqueues the wall-flux reduction of the current state on the lattice's
-// stream and the copy of its six face sums into host_res[8..13].
+// stream; its six face sums go to host_res[8..13].
 static lbm_status nusselt_enqueue(lbm_lattice* h) {
   // chunks per face: about 1024 wall nodes each, at most 64, into the partials
   // buffer (which holds at least one double per 8 nodes, more than 6 x 64
@@ -1173,16 +1173,12 @@ static lbm_status nusselt_enqueue(lbm_lattice* h) {
     const S st_ = make_store<S>(h);
     if (h->parity)
       hipLaunchKernelGGL((k_wall_flux<Lat, S, C, true>), dim3(chunks, 6), dim3(256), 0, h->stream, kp, st_, h->dev_iso,
-                         h->part);
+                         h->part, h->done, h->res + 8, h->host_res + 8);
     else
       hipLaunchKernelGGL((k_wall_flux<Lat, S, C, false>), dim3(chunks, 6), dim3(256), 0, h->stream, kp, st_,
-                         h->dev_iso, h->part);
+                         h->dev_iso, h->part, h->done, h->res + 8, h->host_res + 8);
   });
-  hipLaunchKernelGGL(k_wall_fold, dim3(6), dim3(64), 0, h->stream, h->part, chunks, h->res + 8);
-  lbm_status ls = launch_check("wall flux");
-  if (ls != LBM_OK) return ls;
-  HIP_TRY(hipMemcpyAsync(h->host_res + 8, h->res + 8, 6 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-  return LBM_OK;
+  return launch_check("wall flux");
 }
 
 extern "C" lbm_status lbm_nusselt_start(lbm_lattice* h) {
@@ -1246,12 +1242,10 @@ extern "C" lbm_status lbm_totals(lbm_lattice* h, double* mass, double* heat) {
   });
   lbm_status ls = launch_check("totals");
   if (ls != LBM_OK) return ls;
-  hipLaunchKernelGGL(k_fold_partials, dim3(h->nfold), dim3(h->block), 0, h->stream, h->part, h->nblocks, 0u,
-                     h->part2);
-  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, h->stream, h->part2, h->nfold, h->res + 16);
+  hipLaunchKernelGGL(k_fold<false>, dim3(h->nfold), dim3(256), 0, h->stream, h->part, h->nblocks, h->block, h->part2,
+                     h->done, h->res + 16, h->host_res + 16);
   ls = launch_check("totals final");
   if (ls != LBM_OK) return ls;
-  HIP_TRY(hipMemcpyAsync(h->host_res + 16, h->res + 16, 2 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(hipStreamSynchronize(h->stream));
   // a compare step that follows reuses the partials buffer, so the snapshot stays valid
   if (mass) *mass = (double)h->nodes + h->host_res[16];

@@ -86,10 +86,21 @@ __device__ __forceinline__ const T* again(const T* p) {
   return (const T*)c;
 }
 
-// now: the lattice's step count at the pass (drives FP16 rounding).
+// Stores u and T of node n as a check step's snapshot does.
+template <class C>
+__device__ __forceinline__ void store_macro(const KParams<C>& kp, const Macro<C>& M, C* out, int n) {
+  LBM_GLOBAL C* const o = gbl(out);
+  o[n] = M.ux;
+  o[n + kp.n] = M.uy;
+  o[n + 2 * kp.n] = M.uz;
+  o[n + 3 * kp.n] = M.T;
+}
+
+// now: the lattice's step count at the pass (drives FP16 rounding).  macro1,
+// macro2: where u and T of the state before step 1 / step 2 go, or null.
 template <class Lat, class S, class C, int NT>
 __global__ void __launch_bounds__(NT) k_brick2(const KParams<C>* __restrict__ params, const S src, const S dst, const BrickGrid bg,
-                                               uint32_t now) {
+                                               uint32_t now, C* macro1, C* macro2) {
   using H = typename S::MoveF;
   constexpr int Q = Lat::Q;
   // state between the steps: flow populations as the step carries them, in
@@ -109,6 +120,15 @@ __global__ void __launch_bounds__(NT) k_brick2(const KParams<C>* __restrict__ pa
       gather<Lat, false, false, S, C, false, true>(kp, src, n, nb, h, p);
       const Pairs<Lat, C> P = make_pairs<Lat, C>(h);
       const Macro<C> M = macro<Lat, kFlowScale<S>, C>(kp, P, p);
+      if (macro1) {
+        bool mine = true;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const int at = c[a] - bg.halo[a];
+          mine = mine && at >= 0 && at < bg.b[a] && o[a] + at == x[a];
+        }
+        if (mine) store_macro(kp, M, macro1, n);
+      }
       collide_flow<Lat, C>(kp, M, P, h);
       collide_heat<C>(kp, M, p);
       const uint32_t rnd = kStochastic<S> ? mix32(mix32(now) + (uint32_t)n) : 0u;
@@ -161,9 +181,58 @@ __global__ void __launch_bounds__(NT) k_brick2(const KParams<C>* __restrict__ pa
   });
   const Pairs<Lat, C> P = make_pairs<Lat, C>(h);
   const Macro<C> M = macro<Lat, kFlowScale<S>, C>(kp, P, p);
+  if (macro2) store_macro(kp, M, macro2, n);
   collide_flow<Lat, C>(kp, M, P, h);
   collide_heat<C>(kp, M, p);
   scatter<Lat, true, false, S, C, false, true>(kp, dst, n, nb, h, p, M, kStochastic<S> ? mix32(now + 1u) : 0u);
+}
+
+// The residual of a check whose step ran in a two-step pass: compares the stored
+// u and T (cur) with the snapshot, in the blocks and the order of summation of a
+// compare step of k_step and k_fold, in one launch.
+template <class C>
+__global__ void __launch_bounds__(kMaxBlock) k_compare(const KParams<C>* __restrict__ params,
+                                                       const C* __restrict__ snap, const C* __restrict__ cur,
+                                                       double* part, uint32_t* done, double* res, double* host) {
+  const KParams<C>& kp = *again(params);
+  const int n = blockIdx.x * blockDim.x + threadIdx.x, N = kp.n;
+  double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  if (n < N)
+    residual_terms(kp, cur[n], cur[n + N], cur[n + 2 * N], cur[n + 3 * N], snap[n], snap[n + N], snap[n + 2 * N],
+                   snap[n + 3 * N], v);
+  block_reduce<5>(v, 1u << 4);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int j = 0; j < 5; ++j) part[(size_t)blockIdx.x * kPartStride + j] = v[j];
+  }
+  if (!last_block(done, gridDim.x)) return;
+  // the groups of k_fold, one after another (boxes this small have one or two)
+  double t[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int g = 0; g < (int)gridDim.x; g += (int)blockDim.x) {
+    const int i = g + (int)threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < 5; ++j) v[j] = i < (int)gridDim.x ? part[(size_t)i * kPartStride + j] : 0.0;
+    __syncthreads();
+    block_reduce<5>(v, 1u << 4);
+    // the last stage gives each group to a thread of its own
+    __shared__ double sums[5];
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int j = 0; j < 5; ++j) sums[j] = v[j];
+    }
+    __syncthreads();
+    if ((int)threadIdx.x == g / (int)blockDim.x) {
+#pragma unroll
+      for (int j = 0; j < 5; ++j) t[j] = sums[j];
+    }
+  }
+  __syncthreads();
+  block_reduce<5>(t, 1u << 4);
+  if (threadIdx.x == 0) {
+    finish_residual(t, res);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) host[j] = res[j];
+  }
 }
 
 // T >= 2 steps per launch of an enthalpy lattice (k_step_enthalpy T times): a

@@ -615,6 +615,23 @@ __device__ __forceinline__ void block_reduce(double (&v)[NV], unsigned maxmask) 
 enum : int { kModePlain = 0, kModeSnapshot = 1, kModeCompare = 2, kModeSpan = 3 };
 constexpr int kPartStride = 8;  // doubles per block in the partials buffer
 
+// A node's terms of the residual check: velocity and temperature against their
+// snapshot values s0..s3.
+template <class C>
+__device__ __forceinline__ void residual_terms(const KParams<C>& kp, C cx, C cy, C cz, C cT, C s0, C s1, C s2, C s3,
+                                               double (&red)[5]) {
+  const double ux = cx, uy = cy, uz = cz, T = cT;
+  const double dx = ux - (double)s0, dy = uy - (double)s1, dz = uz - (double)s2;
+  const double dT = (T - (double)s3) * (double)kp.inv_dT;
+  const double th = (T - (double)kp.T_ref) * (double)kp.inv_dT + 0.5;
+  const double uu = ux * ux + uy * uy + uz * uz;
+  red[0] = dx * dx + dy * dy + dz * dz;
+  red[1] = uu;
+  red[2] = dT * dT;
+  red[3] = th * th;
+  red[4] = sqrt(uu);
+}
+
 // One fused time step of the nodes of one block (block index lb of the lattice).
 //   MODE 1 also stores u and T of the pre-collision state into snap (4 planes of n);
 //   MODE 2 also accumulates, per block, sum|u - u_snap|^2, sum|u|^2,
@@ -641,16 +658,7 @@ __device__ __forceinline__ void step_node(const KParams<C>& kp, const S& state, 
   const Macro<C> M = macro<Lat, kFlowScale<S>, C>(kp, P, p);
   LBM_GLOBAL C* sn = gbl(snap);
   if constexpr (MODE == kModeCompare || MODE == kModeSpan) {
-    const double ux = M.ux, uy = M.uy, uz = M.uz, T = M.T;
-    const double dx = ux - (double)sn[n], dy = uy - (double)sn[n + kp.n], dz = uz - (double)sn[n + 2 * kp.n];
-    const double dT = (T - (double)sn[n + 3 * kp.n]) * (double)kp.inv_dT;
-    const double th = (T - (double)kp.T_ref) * (double)kp.inv_dT + 0.5;
-    const double uu = ux * ux + uy * uy + uz * uz;
-    red[0] = dx * dx + dy * dy + dz * dz;
-    red[1] = uu;
-    red[2] = dT * dT;
-    red[3] = th * th;
-    red[4] = sqrt(uu);
+    residual_terms(kp, M.ux, M.uy, M.uz, M.T, sn[n], sn[n + kp.n], sn[n + 2 * kp.n], sn[n + 3 * kp.n], red);
   }
   if constexpr (MODE == kModeSnapshot || MODE == kModeSpan) {
     sn[n] = M.ux;
@@ -974,24 +982,31 @@ static __global__ void __launch_bounds__(64) k_set_clock(uint32_t* clk, int slot
   if (threadIdx.x == 0) gbl(clk)[slot] = value;
 }
 
+// All loads before the first store: the compiler cannot tell the caller's
+// arrays from the state, and a load at a time between dependent stores left the
+// kernel at 4.4 TB/s (128^3 FP32: 148 us).
 template <class Lat, class S, class C>
 __global__ void __launch_bounds__(kMaxBlock) k_set_state(const KParams<C> kp, const S state,
                                                          const double* f_in, const double* g_in) {
   const int n = blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= kp.n) return;
+  double f[Lat::Q], g[7];
+  static_for<0, Lat::Q>([&](auto I) { f[decltype(I)::value] = f_in[(size_t)decltype(I)::value * kp.n + n]; });
+  static_for<0, 7>([&](auto K) { g[decltype(K)::value] = g_in[(size_t)decltype(K)::value * kp.n + n]; });
   static_for<0, Lat::Q>([&](auto I) {
     constexpr int i = decltype(I)::value;
-    const C v = C(f_in[(size_t)i * kp.n + n] - weight<Lat, i>());
+    const C v = C(f[i] - weight<Lat, i>());
     if constexpr (i == 0) st_f0<S, C>(state, (uint32_t)n, v);
     else st_mf<S, C>(state, fslot<Lat>(i, (uint32_t)n), v);
   });
   const double vp = (double)kp.varpi, sT = (double)kp.sigma * (double)kp.T_ref;
-  for (int k = 0; k < 7; ++k) {
+  static_for<0, 7>([&](auto K) {
+    constexpr int k = decltype(K)::value;
     const double om = k == 0 ? 1.0 - vp : vp / 6.0;
-    const C v = C(g_in[(size_t)k * kp.n + n] - om * sT);
-    if (k == 0) st_g0<S, C>(state, (uint32_t)n, v);
+    const C v = C(g[k] - om * sT);
+    if constexpr (k == 0) st_g0<S, C>(state, (uint32_t)n, v);
     else st_mg<S, C>(state, gslot(k, (uint32_t)n), v);
-  }
+  });
 }
 
 // Copies the pre-collision state of lattice `src` (at parity ODD) into lattice

@@ -909,6 +909,11 @@ static size_t population_bytes(const lbm_lattice* h) {
   return static_cast<size_t>(static_cast<char*>(h->snap) - static_cast<char*>(h->buf));
 }
 
+// Bytes of u and T of every node, the last region of a flow lattice's workspace.
+static size_t macro_bytes(const lbm_lattice* h) {
+  return h->energy ? 0 : (size_t)4 * h->nodes * (h->prec == LBM_FP64 ? 8 : 4);
+}
+
 static StateRegions regions(const lbm_lattice* h, void* base) {
   auto at = [&](void* region) { return static_cast<char*>(base) + (static_cast<char*>(region) - static_cast<char*>(h->buf)); };
   return {at(h->mf), at(h->mg), at(h->rs), at(h->r0)};
@@ -924,20 +929,55 @@ extern "C" lbm_status lbm_step_workspace(const lbm_lattice* h, int64_t nsteps, s
     (void)hipGetLastError();
     return LBM_OK;
   }
-  if (cap == hipStreamCaptureStatusNone) *bytes = population_bytes(h);
+  if (cap == hipStreamCaptureStatusNone) *bytes = population_bytes(h) + macro_bytes(h);
   return LBM_OK;
 }
 
-// 2 * passes plain steps of a lattice at parity 0 (passes even).
+// What the step at time t does for the residual check.
+static int step_mode(const lbm_lattice* h, int64_t t) {
+  const int64_t K = h->p.check_interval;
+  if (K <= 0) return kModePlain;
+  if ((t + 1) % K == 0) return kModeSnapshot;
+  if (t > 0 && t % K == 0 && h->snapshot_valid && h->snapshot_at == t - 1) return kModeCompare;
+  return kModePlain;
+}
+
+// 2 * passes steps of a lattice at parity 0 (passes even), their checks included:
+// the pass stores u and T of a snapshot step, or of a compare step into the
+// workspace, where k_compare takes them from.  (With a check every two steps a
+// pass would overwrite the snapshot that its own compare step needs: such
+// lattices take single steps.)
 static lbm_status step_bricks(lbm_lattice* h, int64_t passes, void* ws) {
   const StateRegions home = regions(h, h->buf), away = regions(h, ws);
+  void* const cur = static_cast<char*>(ws) + population_bytes(h);
   const int dim[3] = {h->p.nx, h->p.ny, h->p.nz};
   for (int64_t k = 0; k < passes; ++k) {
+    void* macro[2];
+    int64_t compared = -1;
+    for (int j = 0; j < 2; ++j) {
+      const int64_t t = h->t + j;
+      const int mode = step_mode(h, t);
+      macro[j] = mode == kModeSnapshot ? h->snap : (mode == kModeCompare ? cur : nullptr);
+      if (mode == kModeSnapshot) {
+        h->snapshot_valid = true;
+        h->snapshot_at = t;
+      }
+      if (mode == kModeCompare) {
+        compared = t;
+        h->snapshot_valid = false;
+      }
+    }
     // the member table starts with the lattice's kernel parameters
     launch_brick2(h->q, h->prec, h->dev_member, dim, h->brick, k & 1 ? away : home, k & 1 ? home : away, (uint32_t)h->t,
-                  h->stream);
+                  macro[0], macro[1], h->stream);
     lbm_status ls = launch_check("two-step pass");
     if (ls != LBM_OK) return ls;
+    if (compared >= 0) {
+      launch_compare(h->prec, h->dev_member, h->nodes, h->snap, cur, h->part, h->done, h->res, h->host_res, h->stream);
+      ls = launch_check("residual");
+      if (ls != LBM_OK) return ls;
+      h->last_check = compared;
+    }
     h->t += 2;
   }
   // the step count drives FP16 rounding only
@@ -956,7 +996,7 @@ extern "C" lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size
     const EnthalpyConsts<float> e32 = enthalpy_consts<float>(&h->p);
     using S64 = Store<double, double, double>;
     using S32 = Store<float, float, float>;
-    const bool passes = ws && h->brick.threads && ws_bytes >= population_bytes(h);
+    const bool passes = ws && h->brick.threads && ws_bytes >= population_bytes(h) + macro_bytes(h);
     for (int64_t s = 0; s < nsteps; ++s) {
       const int64_t left = nsteps - s;
       if (passes && h->parity == 0 && left >= 4) {
@@ -989,27 +1029,19 @@ extern "C" lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size
     }
     return LBM_OK;
   }
-  const int64_t K = h->p.check_interval;
-  const bool bricks = ws && h->brick.threads && ws_bytes >= population_bytes(h);
+  const bool bricks = ws && h->brick.threads && (h->p.check_interval == 0 || h->p.check_interval > 2) &&
+                      h->block == 256 &&
+                      ws_bytes >= population_bytes(h) + macro_bytes(h);
   for (int64_t s = 0; s < nsteps; ++s) {
-    int mode = kModePlain;
     const int64_t t = h->t;
-    if (bricks && h->parity == 0 && (K == 0 || t == 0 || t % K != 0)) {
-      // plain steps ahead: up to the snapshot step before the next check
-      int64_t plain = nsteps - s;
-      if (K > 0) plain = std::min(plain, K - 1 - t % K);
-      if (plain >= 4) {
-        const int64_t passes = plain / 4 * 2;
-        lbm_status ls = step_bricks(h, passes, ws);
-        if (ls != LBM_OK) return ls;
-        s += 2 * passes - 1;
-        continue;
-      }
+    const int64_t passes = (nsteps - s) / 2;
+    if (bricks && h->parity == 0 && passes > 0 && passes % 2 == 0) {
+      lbm_status ls = step_bricks(h, passes, ws);
+      if (ls != LBM_OK) return ls;
+      s += 2 * passes - 1;
+      continue;
     }
-    if (K > 0) {
-      if ((t + 1) % K == 0) mode = kModeSnapshot;
-      else if (t > 0 && t % K == 0 && h->snapshot_valid && h->snapshot_at == t - 1) mode = kModeCompare;
-    }
+    const int mode = step_mode(h, t);
     with_types(h, [&](auto lat, auto s_t, auto c_t, const auto& kp) {
       launch_step<decltype(lat), decltype(s_t), decltype(c_t)>(h, kp, mode);
     });

@@ -83,18 +83,21 @@ BrickShape brick_shape(const int dim[3], int prec, int ncu) {
 }
 
 // The same for enthalpy lattices, whose node takes a fraction of the work, so
-// that more steps per pass pay: pass = 4.5 + rounds T (c0 + c1 L / 1024), L the
-// local nodes of the blocks that share a CU.  Measured per step against
-// k_step_enthalpy: 400x6x6 FP64 1.5 / 2.9-4.0 us (T = 6), FP32 1.1 / 4.2 (T = 12),
-// 120x16x15 FP64 2.6 / 4.2, FP32 2.2 / 3.9 (T = 3), but FP64 141x38x37 8.3 / 8.1 and
-// 320x53x53 24 / 16.
+// that more steps per pass pay: step = 4.5 / T + rounds (c0 + c1 L / 1024) + reads
+// of all local nodes at 4.5 TB/s / T, L the local nodes of the blocks that share
+// a CU, against s0 + s1 nodes of k_step_enthalpy.  Measured per step (us, 200
+// steps; the single step's launch floor differs by 1 us between boxes): 400x6x6
+// FP64 1.5 / 2.9-3.8, FP32 1.1 / 2.7-3.9, 1000x6x5 1.6 / 3.3-4.1 and 1.2 / 3.0-3.6, 640x8x8
+// 2.5 / 3.2-4.0 and 1.8 / 3.1-3.8, 120x16x15 3.0 / 3.3-4.0 and 2.4 / 2.8-3.8, but 158x21x20
+// (66k nodes) 4.3 / 4.2-4.8 and 4.0 / 3.4-4.1, 100x36x36 7.1 / 5.8-6.1 and 5.5 / 4.1-4.8:
+// hence the node limit.
 BrickShape brick_shape_enthalpy(const int dim[3], int prec, int ncu) {
   const bool fp64 = prec == LBM_FP64;
   const long long nodes = (long long)dim[0] * dim[1] * dim[2];
   BrickShape best;
-  if (nodes > 150000) return best;
+  if (nodes > 60000) return best;
   const double c0 = fp64 ? 0.35 : 0.3, c1 = fp64 ? 0.9 : 0.45;
-  double least = 0.85 * (fp64 ? 3.0 + 2.2e-5 * nodes : 3.2 + 1.3e-5 * nodes);
+  double least = 0.93 * (fp64 ? 2.9 + 2.3e-5 * nodes : 2.65 + 1.15e-5 * nodes);
   const int edges[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 0};  // 0: the whole axis
   for (int T : {2, 3, 4, 6, 8, 12})
     for (int ex : edges)
@@ -118,7 +121,9 @@ BrickShape brick_shape_enthalpy(const int dim[3], int prec, int ncu) {
           const long long per_cu = (blocks + ncu - 1) / ncu;
           const long long rounds = (per_cu + share - 1) / share;
           const double local = (double)std::min<long long>(share, per_cu) * e;
-          double t = 4.5 / T + rounds * (c0 + c1 * local / 1024.0);
+          double t = 4.5 / T + rounds * (c0 + c1 * local / 1024.0) +
+                     (double)blocks * e * (fp64 ? 56.0 : 28.0) / 4.5e6 / T;
+          if (rounds > 1) t *= fp64 ? 1.15 : 1.35;
           if (b[0] < dim[0] && b[0] < 8) t *= 1.1;  // short rows
           if (t < least) {
             least = t;
@@ -146,34 +151,51 @@ static BrickGrid brick_grid(const int dim[3], const BrickShape& s, int layers) {
 
 template <class Lat, class S, class C, int NT>
 static void launch_brick2_nt(const void* params, const int dim[3], const BrickShape& s, const StateRegions& src,
-                             const StateRegions& dst, uint32_t now, hipStream_t stream) {
+                             const StateRegions& dst, uint32_t now, void* macro1,
+                             void* macro2, hipStream_t stream) {
   const dim3 grid((dim[0] + s.b[0] - 1) / s.b[0], (dim[1] + s.b[1] - 1) / s.b[1], (dim[2] + s.b[2] - 1) / s.b[2]);
   hipLaunchKernelGGL((k_brick2<Lat, S, C, NT>), grid, dim3(NT), 0, stream, static_cast<const KParams<C>*>(params), store_of<S>(src), store_of<S>(dst),
-                     brick_grid(dim, s, 1), now);
+                     brick_grid(dim, s, 1), now, static_cast<C*>(macro1), static_cast<C*>(macro2));
 }
 
 template <class Lat, class S, class C>
 static void launch_brick2_of(const void* params, const int dim[3], const BrickShape& s, const StateRegions& src,
-                             const StateRegions& dst, uint32_t now, hipStream_t stream) {
-  if (s.threads == 256) launch_brick2_nt<Lat, S, C, 256>(params, dim, s, src, dst, now, stream);
-  else if (s.threads == 512) launch_brick2_nt<Lat, S, C, 512>(params, dim, s, src, dst, now, stream);
-  else launch_brick2_nt<Lat, S, C, 768>(params, dim, s, src, dst, now, stream);
+                             const StateRegions& dst, uint32_t now, void* macro1,
+                             void* macro2, hipStream_t stream) {
+  if (s.threads == 256) launch_brick2_nt<Lat, S, C, 256>(params, dim, s, src, dst, now, macro1, macro2, stream);
+  else if (s.threads == 512) launch_brick2_nt<Lat, S, C, 512>(params, dim, s, src, dst, now, macro1, macro2, stream);
+  else launch_brick2_nt<Lat, S, C, 768>(params, dim, s, src, dst, now, macro1, macro2, stream);
 }
 
 void launch_brick2(int q, int prec, const void* params, const int dim[3], const BrickShape& shape,
-                   const StateRegions& src, const StateRegions& dst, uint32_t now, hipStream_t stream) {
+                   const StateRegions& src, const StateRegions& dst, uint32_t now, void* macro1,
+                             void* macro2, hipStream_t stream) {
   using S64 = Store<double, double, double>;
   using S32 = Store<float, float, float>;
   using S16 = Store<_Float16, float, float>;
   if (q == 19) {
-    if (prec == LBM_FP64) launch_brick2_of<D3Q19, S64, double>(params, dim, shape, src, dst, now, stream);
-    else if (prec == LBM_FP32) launch_brick2_of<D3Q19, S32, float>(params, dim, shape, src, dst, now, stream);
-    else launch_brick2_of<D3Q19, S16, float>(params, dim, shape, src, dst, now, stream);
+    if (prec == LBM_FP64) launch_brick2_of<D3Q19, S64, double>(params, dim, shape, src, dst, now, macro1, macro2, stream);
+    else if (prec == LBM_FP32) launch_brick2_of<D3Q19, S32, float>(params, dim, shape, src, dst, now, macro1, macro2, stream);
+    else launch_brick2_of<D3Q19, S16, float>(params, dim, shape, src, dst, now, macro1, macro2, stream);
   } else {
-    if (prec == LBM_FP64) launch_brick2_of<D3Q15, S64, double>(params, dim, shape, src, dst, now, stream);
-    else if (prec == LBM_FP32) launch_brick2_of<D3Q15, S32, float>(params, dim, shape, src, dst, now, stream);
-    else launch_brick2_of<D3Q15, S16, float>(params, dim, shape, src, dst, now, stream);
+    if (prec == LBM_FP64) launch_brick2_of<D3Q15, S64, double>(params, dim, shape, src, dst, now, macro1, macro2, stream);
+    else if (prec == LBM_FP32) launch_brick2_of<D3Q15, S32, float>(params, dim, shape, src, dst, now, macro1, macro2, stream);
+    else launch_brick2_of<D3Q15, S16, float>(params, dim, shape, src, dst, now, macro1, macro2, stream);
   }
+}
+
+template <class C>
+static void launch_compare_of(const void* params, int nodes, const void* snap, const void* cur, double* part,
+                              uint32_t* done, double* res, double* host, hipStream_t stream) {
+  hipLaunchKernelGGL((k_compare<C>), dim3((nodes + 255) / 256), dim3(256), 0, stream,
+                     static_cast<const KParams<C>*>(params), static_cast<const C*>(snap), static_cast<const C*>(cur),
+                     part, done, res, host);
+}
+
+void launch_compare(int prec, const void* params, int nodes, const void* snap, const void* cur, double* part,
+                    uint32_t* done, double* res, double* host, hipStream_t stream) {
+  if (prec == LBM_FP64) launch_compare_of<double>(params, nodes, snap, cur, part, done, res, host, stream);
+  else launch_compare_of<float>(params, nodes, snap, cur, part, done, res, host, stream);
 }
 
 template <class C, int NT>

@@ -35,7 +35,15 @@ void launch_brick_enthalpy(const KParams<double>& kp, const EnthalpyConsts<doubl
 
 // Two time steps src -> dst (natural layout) of a lattice with q = 19 or 15
 // flow populations at step count `now`; params: its KParams in device memory.
+// macro1, macro2 (or null): where u and T before each step go (4 planes of nodes
+// in the compute type).
 void launch_brick2(int q, int prec, const void* params, const int dim[3], const BrickShape& shape,
-                   const StateRegions& src, const StateRegions& dst, uint32_t now, hipStream_t stream);
+                   const StateRegions& src, const StateRegions& dst, uint32_t now, void* macro1, void* macro2,
+                   hipStream_t stream);
+
+// Residual check of u and T in `cur` against `snap` (as a compare step and k_fold
+// make it with blocks of 256), into res and its host mirror.
+void launch_compare(int prec, const void* params, int nodes, const void* snap, const void* cur, double* part,
+                    uint32_t* done, double* res, double* host, hipStream_t stream);
 
 }  // namespace lbm

@@ -73,6 +73,20 @@ def test_two_steps_per_launch_equal_single_steps(name, prec):
             assert a.time == b.time and a.residual() == b.residual()
 
 
+@pytest.mark.parametrize("interval", [1, 2, 3, 4, 10])
+def test_checks_inside_passes_equal_single_steps(interval):
+    """Snapshot and compare steps on either side of a pass, at each alignment."""
+    wl = lbm_inputs.cavity((40, 21, 24), rayleigh=1e4, seed=6)
+    _say(f"case checks every {interval}")
+    with Lattice(wl, "fp64", check_interval=interval) as a, Lattice(wl, "fp64", check_interval=interval) as b:
+        for n in (4, 21, 6, 20, 1, 13):
+            _single(a, n)
+            b.step(n)
+            assert a.residual() == b.residual(), (interval, a.time)
+            for x, y in zip(a.get_state(), b.get_state()):
+                assert torch.equal(x, y), (interval, a.time)
+
+
 MELT = {
     "slab": ((400, 6, 6), None),
     "walls": ((30, 4, 11), [HOT, WALL, WALL, COLD, PER, PER]),

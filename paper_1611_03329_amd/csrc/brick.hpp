@@ -203,7 +203,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_compare(const KParams<C>* __restr
   block_reduce<5>(v, 1u << 4);
   if (threadIdx.x == 0) {
 #pragma unroll
-    for (int j = 0; j < 5; ++j) part[(size_t)blockIdx.x * kPartStride + j] = v[j];
+    for (int j = 0; j < 5; ++j) st_agent(part + (size_t)blockIdx.x * kPartStride + j, v[j]);
   }
   if (!last_block(done, gridDim.x)) return;
   // the groups of k_fold, one after another (boxes this small have one or two)
@@ -211,7 +211,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_compare(const KParams<C>* __restr
   for (int g = 0; g < (int)gridDim.x; g += (int)blockDim.x) {
     const int i = g + (int)threadIdx.x;
 #pragma unroll
-    for (int j = 0; j < 5; ++j) v[j] = i < (int)gridDim.x ? part[(size_t)i * kPartStride + j] : 0.0;
+    for (int j = 0; j < 5; ++j) v[j] = i < (int)gridDim.x ? ld_agent(part + (size_t)i * kPartStride + j) : 0.0;
     __syncthreads();
     block_reduce<5>(v, 1u << 4);
     // the last stage gives each group to a thread of its own

@@ -717,18 +717,28 @@ __device__ __forceinline__ void step_block(const KParams<C>& kp, const S& state,
   }
 }
 
-// Whether this block is the last of `total` to get here (thread 0's earlier
-// stores are then visible to the caller from every block).  The last block
+// Partial results that another block of the same launch reads go past the XCD's
+// L2 (agent scope, which the L2 caches of the XCDs share no lines for).  A fence
+// instead would write back a whole L2 per block: with 100 blocks it took 10 us.
+__device__ __forceinline__ void st_agent(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double ld_agent(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Whether this block is the last of `total` to get here; what thread 0 of each
+// block stored before with st_agent, the last block reads with ld_agent.  It
 // leaves *count at 0 for the next launch.
 __device__ __forceinline__ bool last_block(uint32_t* count, uint32_t total) {
   __shared__ int last;
   if (threadIdx.x == 0) {
-    __threadfence();
-    last = __hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == total - 1;
+    // the stores are complete at agent scope once they are counted down
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    last = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1;
     if (last) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
-  if (last) __threadfence();
   return last;
 }
 
@@ -774,7 +784,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_fold(const double* __restrict__ i
   block_reduce<NV>(v, maxmask);
   if (threadIdx.x == 0) {
 #pragma unroll
-    for (int j = 0; j < NV; ++j) part2[(size_t)blockIdx.x * kPartStride + j] = v[j];
+    for (int j = 0; j < NV; ++j) st_agent(part2 + (size_t)blockIdx.x * kPartStride + j, v[j]);
   }
   if (!last_block(done, gridDim.x)) return;
 #pragma unroll
@@ -782,7 +792,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_fold(const double* __restrict__ i
   for (int b = threadIdx.x; b < (int)gridDim.x; b += blockDim.x) {
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-      const double w = part2[(size_t)b * kPartStride + j];
+      const double w = ld_agent(part2 + (size_t)b * kPartStride + j);
       v[j] = ((maxmask >> j) & 1u) ? pick_max(v[j], w) : v[j] + w;
     }
   }
@@ -943,11 +953,11 @@ __global__ void __launch_bounds__(kMaxBlock) k_wall_flux(const KParams<C> kp, co
   }
   block_reduce<1>(v, 0u);
   const int chunks = (int)gridDim.x;
-  if (threadIdx.x == 0) part[face * chunks + (int)blockIdx.x] = v[0];
+  if (threadIdx.x == 0) st_agent(part + face * chunks + (int)blockIdx.x, v[0]);
   if (!last_block(done, gridDim.x * gridDim.y) || threadIdx.x >= 6) return;
   const int f = (int)threadIdx.x;
   double s = 0.0;
-  for (int b = 0; b < chunks; ++b) s += part[f * chunks + b];
+  for (int b = 0; b < chunks; ++b) s += ld_agent(part + f * chunks + b);
   out[f] = host[f] = s;
 }
 
@@ -982,31 +992,49 @@ static __global__ void __launch_bounds__(64) k_set_clock(uint32_t* clk, int slot
   if (threadIdx.x == 0) gbl(clk)[slot] = value;
 }
 
-// All loads before the first store: the compiler cannot tell the caller's
-// arrays from the state, and a load at a time between dependent stores left the
-// kernel at 4.4 TB/s (128^3 FP32: 148 us).
+// Block (b, i) converts population i (then the temperature populations) of
+// kSetNodes nodes.  Plane by plane the caller's arrays and the state are streamed;
+// a thread per node read 26 planes at once, which for boxes whose planes lie a
+// power of two apart hit few memory channels (128^3 FP32: 148 us, 4.4 TB/s).
+constexpr int kSetNodes = 4 * kMaxBlock;
+
 template <class Lat, class S, class C>
 __global__ void __launch_bounds__(kMaxBlock) k_set_state(const KParams<C> kp, const S state,
-                                                         const double* f_in, const double* g_in) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= kp.n) return;
-  double f[Lat::Q], g[7];
-  static_for<0, Lat::Q>([&](auto I) { f[decltype(I)::value] = f_in[(size_t)decltype(I)::value * kp.n + n]; });
-  static_for<0, 7>([&](auto K) { g[decltype(K)::value] = g_in[(size_t)decltype(K)::value * kp.n + n]; });
-  static_for<0, Lat::Q>([&](auto I) {
-    constexpr int i = decltype(I)::value;
-    const C v = C(f[i] - weight<Lat, i>());
-    if constexpr (i == 0) st_f0<S, C>(state, (uint32_t)n, v);
-    else st_mf<S, C>(state, fslot<Lat>(i, (uint32_t)n), v);
-  });
-  const double vp = (double)kp.varpi, sT = (double)kp.sigma * (double)kp.T_ref;
-  static_for<0, 7>([&](auto K) {
-    constexpr int k = decltype(K)::value;
+                                                         const double* __restrict__ f_in,
+                                                         const double* __restrict__ g_in) {
+  const int i = (int)blockIdx.y, n0 = (int)blockIdx.x * kSetNodes + (int)threadIdx.x;
+  const bool flow = i < Lat::Q;
+  const double* const in = flow ? f_in + (size_t)i * kp.n : g_in + (size_t)(i - Lat::Q) * kp.n;
+  double v[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int n = n0 + j * kMaxBlock;
+    v[j] = n < kp.n ? in[n] : 0.0;
+  }
+  if (flow) {
+    // one weight per speed: directions 1 to 6 lie along an axis
+    const double w = i == 0 ? weight<Lat, 0>() : (i < 7 ? weight<Lat, 1>() : weight<Lat, 7>());
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int n = n0 + j * kMaxBlock;
+      if (n >= kp.n) break;
+      const C x = C(v[j] - w);
+      if (i == 0) st_f0<S, C>(state, (uint32_t)n, x);
+      else st_mf<S, C>(state, fslot<Lat>(i, (uint32_t)n), x);
+    }
+  } else {
+    const int k = i - Lat::Q;
+    const double vp = (double)kp.varpi, sT = (double)kp.sigma * (double)kp.T_ref;
     const double om = k == 0 ? 1.0 - vp : vp / 6.0;
-    const C v = C(g[k] - om * sT);
-    if constexpr (k == 0) st_g0<S, C>(state, (uint32_t)n, v);
-    else st_mg<S, C>(state, gslot(k, (uint32_t)n), v);
-  });
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int n = n0 + j * kMaxBlock;
+      if (n >= kp.n) break;
+      const C x = C(v[j] - om * sT);
+      if (k == 0) st_g0<S, C>(state, (uint32_t)n, x);
+      else st_mg<S, C>(state, gslot(k, (uint32_t)n), x);
+    }
+  }
 }
 
 // Copies the pre-collision state of lattice `src` (at parity ODD) into lattice

@@ -1361,8 +1361,8 @@ extern "C" lbm_status lbm_set_state(lbm_lattice* h, const double* f, const doubl
     using Lat = decltype(lat);
     using S = decltype(s_t);
     using C = decltype(c_t);
-    hipLaunchKernelGGL((k_set_state<Lat, S, C>), dim3(h->nblocks), dim3(h->block), 0, h->stream, kp,
-                       make_store<S>(h), df, dg);
+    hipLaunchKernelGGL((k_set_state<Lat, S, C>), dim3((h->nodes + kSetNodes - 1) / kSetNodes, Lat::Q + 7),
+                       dim3(kMaxBlock), 0, h->stream, kp, make_store<S>(h), df, dg);
   });
   st = launch_check("set_state");
   if (st != LBM_OK) return st;

@@ -234,6 +234,10 @@ class Lattice:
                                ctypes.byref(h)))
         self._h = h
         self.batch = None
+        # whether long runs of steps take a workspace (lbm_step_workspace)
+        need = ctypes.c_size_t()
+        _check(_lib.lbm_step_workspace(h, 1 << 30, ctypes.byref(need)))
+        self._passes = need.value > 0
 
     # -- lifetime
     def close(self):
@@ -269,7 +273,8 @@ class Lattice:
         one by one."""
         n = int(n)
         need = ctypes.c_size_t()
-        _check(_lib.lbm_step_workspace(self._h, n, ctypes.byref(need)))
+        if self._passes and n >= 4:
+            _check(_lib.lbm_step_workspace(self._h, n, ctypes.byref(need)))
         if need.value:
             try:
                 # freed when this returns: the allocator hands it out again in the
@@ -383,8 +388,10 @@ class Lattice:
         if f is not None:
             f = arr(f, self.q)
         _check(_lib.lbm_set_state(self._h, _ptr(f), _ptr(g)))
-        # keep the inputs alive until the copy kernel has run
-        self.stream.synchronize()
+        # on another stream than the caller's, the inputs must stay as they are
+        # until the copy kernel has run; on the caller's own, order does that
+        if self.stream.cuda_stream != torch.cuda.current_stream(self.device).cuda_stream:
+            self.stream.synchronize()
 
 
 class Batch:

@@ -51,7 +51,9 @@ struct lbm_lattice {
   lbm_derived d;
   hipStream_t stream = nullptr;
   int device = 0;  // the device current at creation: the lattice's memory lives there
-  BrickShape brick;  // bricks of its two-step passes (lbm_step_ws), if it takes any
+  BrickShape brick;  // bricks of its passes of several steps (lbm_step_ws), if it takes any
+  int march = 0;       // large enthalpy lattices: the variant of k_march2's two-step passes
+  int ncu = 0;         // compute units of the device
   void* buf = nullptr;
   bool owns_buf = false;
   size_t bytes = 0;
@@ -731,16 +733,13 @@ extern "C" lbm_status lbm_create(const lbm_params* p, void* dev_buf, size_t byte
   fill_kparams<float>(p, &d, h->nodes, h->pstride, &h->kf);
   h->even_lds = even_step_lds(p, h->kf, h->nodes);
   h->nxcd = xcd_ranges_for(p, L);
-  if (h->energy) {
-    const int dim[3] = {p->nx, p->ny, p->nz};
-    int ncu = 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && ncu > 0)
-      h->brick = brick_shape_enthalpy(dim, p->precision, ncu);
-  } else if (!(h->kd.moving || h->kd.open_flow || h->kd.open_heat)) {
-    const int dim[3] = {p->nx, p->ny, p->nz};
-    int ncu = 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && ncu > 0)
-      h->brick = brick_shape(dim, p->precision, ncu);
+  const int dim[3] = {p->nx, p->ny, p->nz};
+  if (hipDeviceGetAttribute(&h->ncu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) h->ncu = 0;
+  if (h->ncu > 0 && h->energy) {
+    h->brick = brick_shape_enthalpy(dim, p->precision, h->ncu);
+    h->march = h->brick.threads ? 0 : march_variant(dim, p->precision);
+  } else if (h->ncu > 0 && !(h->kd.moving || h->kd.open_flow || h->kd.open_heat)) {
+    h->brick = brick_shape(dim, p->precision, h->ncu);
   }
 
   int iso[6];
@@ -922,7 +921,7 @@ static StateRegions regions(const lbm_lattice* h, void* base) {
 extern "C" lbm_status lbm_step_workspace(const lbm_lattice* h, int64_t nsteps, size_t* bytes) {
   if (!h || !bytes) return fail(LBM_ERR_INVALID_ARG, "NULL argument");
   *bytes = 0;
-  if (nsteps < 4 || h->batch || !h->brick.threads) return LBM_OK;
+  if (nsteps < 4 || h->batch || (!h->brick.threads && !h->march)) return LBM_OK;
   // a captured call would tie the graph to a workspace that is only lent
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (h->stream && hipStreamIsCapturing(h->stream, &cap) != hipSuccess) {
@@ -996,23 +995,30 @@ extern "C" lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size
     const EnthalpyConsts<float> e32 = enthalpy_consts<float>(&h->p);
     using S64 = Store<double, double, double>;
     using S32 = Store<float, float, float>;
-    const bool passes = ws && h->brick.threads && ws_bytes >= population_bytes(h) + macro_bytes(h);
+    const int most = h->march ? 2 : h->brick.steps;  // steps per pass
+    const bool lent = ws && most > 0 && ws_bytes >= population_bytes(h) + macro_bytes(h);
     for (int64_t s = 0; s < nsteps; ++s) {
+      // an even number of passes: k_march2 takes two steps each, bricks about
+      // equal numbers
       const int64_t left = nsteps - s;
-      if (passes && h->parity == 0 && left >= 4) {
-        // an even number of passes of about equal length
-        const int64_t n = (left + 2 * h->brick.steps - 1) / (2 * h->brick.steps) * 2;
+      const int64_t passes = h->march || most == 0 ? left / 2 : (left + 2 * most - 1) / (2 * most) * 2;
+      if (lent && h->parity == 0 && left >= 4 && passes % 2 == 0) {
         const StateRegions home = regions(h, h->buf), away = regions(h, ws);
-        for (int64_t k = 0; k < n; ++k) {
-          const int steps = (int)(left * (k + 1) / n - left * k / n);
+        int64_t taken = 0;
+        for (int64_t k = 0; k < passes; ++k) {
+          const int steps = h->march ? 2 : (int)(left * (k + 1) / passes - left * k / passes);
           const StateRegions &src = k & 1 ? away : home, &dst = k & 1 ? home : away;
-          if (h->prec == LBM_FP64) launch_brick_enthalpy(h->kd, e64, h->brick, steps, src, dst, h->stream);
+          if (h->march && h->prec == LBM_FP64) launch_march2(h->kd, e64, src, dst, h->march, h->ncu, h->stream);
+          else if (h->march) launch_march2(h->kf, e32, src, dst, h->march, h->ncu, h->stream);
+          else if (h->prec == LBM_FP64) launch_brick_enthalpy(h->kd, e64, h->brick, steps, src, dst, h->stream);
           else launch_brick_enthalpy(h->kf, e32, h->brick, steps, src, dst, h->stream);
           lbm_status ls = launch_check("enthalpy pass");
           if (ls != LBM_OK) return ls;
           h->t += steps;
+          taken += steps;
         }
-        return LBM_OK;
+        s += taken - 1;
+        continue;
       }
       const dim3 g(h->nblocks), b(h->block);
       if (h->prec == LBM_FP64) {

@@ -5,6 +5,7 @@
 
 #include "brick.hpp"
 #include "lbm.h"
+#include "march.hpp"
 
 namespace lbm {
 
@@ -99,29 +100,32 @@ BrickShape brick_shape_enthalpy(const int dim[3], int prec, int ncu) {
   const double c0 = fp64 ? 0.35 : 0.3, c1 = fp64 ? 0.9 : 0.45;
   double least = 0.93 * (fp64 ? 2.9 + 2.3e-5 * nodes : 2.65 + 1.15e-5 * nodes);
   const int edges[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 0};  // 0: the whole axis
-  for (int T : {2, 3, 4, 6, 8, 12})
-    for (int ex : edges)
-      for (int ey : edges)
+  for (int T : {2, 3, 4, 6, 8, 12}) {
+    // edge b along axis a and the local edge around it; 0 where it does not fit:
+    // a brick that does not span its axis needs T - 1 layers of other nodes
+    auto local = [&](int a, int want, int& b) {
+      b = want == 0 ? dim[a] : want;
+      if (want == 0) return b;
+      return b < dim[a] && T - 1 <= dim[a] ? b + 2 * (T - 1) : 0;
+    };
+    int b[3];
+    for (int ex : edges) {
+      const int e0 = local(0, ex, b[0]);
+      if (e0 == 0 || e0 > 1024) continue;
+      for (int ey : edges) {
+        const int e1 = local(1, ey, b[1]);
+        if (e1 == 0 || e1 > 1024 / e0) continue;
         for (int ez : edges) {
-          const int want[3] = {ex, ey, ez};
-          int b[3];
-          bool ok = true;
-          for (int a = 0; a < 3; ++a) {
-            b[a] = want[a] == 0 ? dim[a] : want[a];
-            // a brick that does not span its axis needs T - 1 layers of other nodes
-            ok = ok && (want[a] == 0 || (b[a] < dim[a] && T - 1 <= dim[a]));
-          }
-          if (!ok || b[0] > 1024 || b[1] > 1024 || b[2] > 1024) continue;
-          if ((long long)b[0] * b[1] * b[2] > 1024) continue;
-          const int e = local_nodes(dim, b, T - 1);
-          if (e > 1024) continue;
+          const int e2 = local(2, ez, b[2]);
+          if (e2 == 0 || e2 > 1024 / (e0 * e1)) continue;
+          const int e = e0 * e1 * e2;
           const int threads = e <= 256 ? 256 : (e <= 512 ? 512 : 1024);
           const int share = (fp64 ? 1 : 2) * (1024 / threads);
           const long long blocks = (long long)cuts(dim[0], b[0]) * cuts(dim[1], b[1]) * cuts(dim[2], b[2]);
           const long long per_cu = (blocks + ncu - 1) / ncu;
           const long long rounds = (per_cu + share - 1) / share;
-          const double local = (double)std::min<long long>(share, per_cu) * e;
-          double t = 4.5 / T + rounds * (c0 + c1 * local / 1024.0) +
+          const double local_nodes = (double)std::min<long long>(share, per_cu) * e;
+          double t = 4.5 / T + rounds * (c0 + c1 * local_nodes / 1024.0) +
                      (double)blocks * e * (fp64 ? 56.0 : 28.0) / 4.5e6 / T;
           if (rounds > 1) t *= fp64 ? 1.15 : 1.35;
           if (b[0] < dim[0] && b[0] < 8) t *= 1.1;  // short rows
@@ -132,6 +136,9 @@ BrickShape brick_shape_enthalpy(const int dim[3], int prec, int ncu) {
             best.steps = T;
           }
         }
+      }
+    }
+  }
   return best;
 }
 
@@ -223,6 +230,62 @@ void launch_brick_enthalpy(const KParams<float>& kp, const EnthalpyConsts<float>
 void launch_brick_enthalpy(const KParams<double>& kp, const EnthalpyConsts<double>& ec, const BrickShape& shape,
                            int steps, const StateRegions& src, const StateRegions& dst, hipStream_t stream) {
   launch_brick_enthalpy_of(kp, ec, shape, steps, src, dst, stream);
+}
+
+// The variant of k_march2 an enthalpy lattice takes (0: none).  A lane's vector
+// needs x edges that it divides.  FP64 pays from 2^18 nodes on (300x33x33 10.0 ->
+// 9.2 us per step, 256x64x64 18.5 -> 15.4, 128^3 34.9 -> 25.6), FP32 from 2^20 (256x64x64
+// 11.7 -> 10.5, 400x100x100 34.9 -> 26.8; but 320x53x53 10.4 -> 11.5).  FP32 states that
+// stay out of the last-level cache run better in 1 KB rows of four nodes per
+// lane (1024x128x128 109 against 113 us, 740x112x113 72 against 81), if the rows are
+// filled; cached ones in 512 B rows, of which the box makes more (128^3 15.2
+// against 22.7, 400x100x100 26.8 against 28.6).
+int march_variant(const int dim[3], int prec) {
+  const long long nodes = (long long)dim[0] * dim[1] * dim[2];
+  if (prec == LBM_FP64) return nodes >= (1 << 18) && dim[0] % 2 == 0 ? 2 : 0;
+  if (nodes < (1 << 20) || dim[0] % 2 != 0) return 0;
+  const bool wide = dim[0] % 4 == 0 && 4 * dim[0] >= 3 * 256 * cuts(dim[0], 256);
+  return wide && nodes >= 6'000'000 ? 4 : 2;
+}
+
+// Columns and the number of z ranges that finishes first when each CU takes one
+// item at a time (a range of P planes costs P + 2: step 1 runs on a plane more
+// at each end).
+static MarchGrid march_grid(const int dim[3], int row, int rows, int ncu) {
+  MarchGrid g;
+  g.tiles_x = cuts(dim[0], row);
+  g.tiles_y = cuts(dim[1], rows - 2);
+  const long long tiles = (long long)g.tiles_x * g.tiles_y;
+  long long best = -1;
+  g.chunks = 1;
+  for (int k = 1; k <= dim[2] && k <= 64; ++k) {
+    const long long cost = (tiles * k + ncu - 1) / ncu * (cuts(dim[2], k) + 3);
+    if (best < 0 || cost < best) best = cost, g.chunks = k;
+  }
+  g.items = (int)tiles * g.chunks;
+  g.per_xcd = cuts(g.items, 8);
+  return g;
+}
+
+template <class C, int V, int R>
+static void launch_march2_of(const KParams<C>& kp, const EnthalpyConsts<C>& ec, const StateRegions& src,
+                             const StateRegions& dst, int ncu, hipStream_t stream) {
+  const int dim[3] = {kp.nx, kp.ny, kp.nz};
+  const MarchGrid g = march_grid(dim, 64 * V, R, ncu);
+  const int per = std::min(g.per_xcd, std::max(1, ncu / 8));
+  using S = Store<C, C, C>;
+  hipLaunchKernelGGL((k_march2<C, V, R>), dim3(8 * per), dim3(march_threads(R)), 0, stream, kp, ec, store_of<S>(src),
+                     store_of<S>(dst), g);
+}
+
+void launch_march2(const KParams<float>& kp, const EnthalpyConsts<float>& ec, const StateRegions& src,
+                   const StateRegions& dst, int variant, int ncu, hipStream_t stream) {
+  if (variant == 4) launch_march2_of<float, 4, 11>(kp, ec, src, dst, ncu, stream);
+  else launch_march2_of<float, 2, 15>(kp, ec, src, dst, ncu, stream);
+}
+void launch_march2(const KParams<double>& kp, const EnthalpyConsts<double>& ec, const StateRegions& src,
+                   const StateRegions& dst, int, int ncu, hipStream_t stream) {
+  launch_march2_of<double, 2, 11>(kp, ec, src, dst, ncu, stream);
 }
 
 }  // namespace lbm

@@ -33,6 +33,14 @@ void launch_brick_enthalpy(const KParams<float>& kp, const EnthalpyConsts<float>
 void launch_brick_enthalpy(const KParams<double>& kp, const EnthalpyConsts<double>& ec, const BrickShape& shape,
                            int steps, const StateRegions& src, const StateRegions& dst, hipStream_t stream);
 
+// Nodes per lane of the two-step pass that a large enthalpy lattice takes, 0 if
+// it takes none; launch_march2 makes the pass.
+int march_variant(const int dim[3], int prec);
+void launch_march2(const KParams<float>& kp, const EnthalpyConsts<float>& ec, const StateRegions& src,
+                   const StateRegions& dst, int variant, int ncu, hipStream_t stream);
+void launch_march2(const KParams<double>& kp, const EnthalpyConsts<double>& ec, const StateRegions& src,
+                   const StateRegions& dst, int variant, int ncu, hipStream_t stream);
+
 // Two time steps src -> dst (natural layout) of a lattice with q = 19 or 15
 // flow populations at step count `now`; params: its KParams in device memory.
 // macro1, macro2 (or null): where u and T before each step go (4 planes of nodes

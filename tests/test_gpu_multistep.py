@@ -149,3 +149,33 @@ def test_steps_in_a_captured_graph_equal_eager_steps():
                 torch.cuda.synchronize()
                 for x, y in zip(a.get_state(), b.get_state()):
                     assert torch.equal(x, y)
+
+
+MARCH = {
+    # FP32: rows of 64 lanes x 2 and x 4 nodes, FP64: x 2
+    "wide_rows": ((1040, 79, 75), [HOT, COLD, PER, PER, PER, PER]),
+    "one_row": ((256, 65, 64), [WALL, HOT, COLD, WALL, WALL, HOT]),
+    "ragged": ((258, 55, 75), [PER, PER, HOT, WALL, PER, PER]),
+    "periodic": ((1026, 33, 31), [PER] * 6),
+    "thin": ((4096, 257, 1), [HOT, WALL, PER, PER, COLD, HOT]),
+}
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("name", sorted(MARCH))
+def test_enthalpy_marching_passes_equal_single_steps(name, prec):
+    shape, faces = MARCH[name]
+    wl = lbm_inputs.melting(*shape, alpha_ratio=12.0)
+    wl["faces"] = faces
+    _say(f"case enthalpy marching passes {name} {prec}")
+    with Lattice(wl, prec) as a, Lattice(wl, prec) as b:
+        g = torch.rand((7,) + a.shape, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(3))
+        g = 0.6 * g - 0.3
+        a.set_state(None, g)
+        b.set_state(None, g)
+        assert _workspace(b) > 0
+        for n in (4, 7, 6):
+            _single(a, n)
+            b.step(n)
+            assert torch.equal(a.get_state()[1], b.get_state()[1]), (name, prec, n)
+            assert a.time == b.time

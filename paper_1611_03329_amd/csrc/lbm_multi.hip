@@ -232,20 +232,25 @@ void launch_brick_enthalpy(const KParams<double>& kp, const EnthalpyConsts<doubl
   launch_brick_enthalpy_of(kp, ec, shape, steps, src, dst, stream);
 }
 
-// The variant of k_march2 an enthalpy lattice takes (0: none).  A lane's vector
-// needs x edges that it divides.  FP64 pays from 2^18 nodes on (300x33x33 10.0 ->
-// 9.2 us per step, 256x64x64 18.5 -> 15.4, 128^3 34.9 -> 25.6), FP32 from 2^20 (256x64x64
-// 11.7 -> 10.5, 400x100x100 34.9 -> 26.8; but 320x53x53 10.4 -> 11.5).  FP32 states that
-// stay out of the last-level cache run better in 1 KB rows of four nodes per
-// lane (1024x128x128 109 against 113 us, 740x112x113 72 against 81), if the rows are
-// filled; cached ones in 512 B rows, of which the box makes more (128^3 15.2
-// against 22.7, 400x100x100 26.8 against 28.6).
+// The variant of k_march2 an enthalpy lattice takes (0: none; 4: FP32 with four
+// nodes per lane, FP64 with two, both with streaming stores; 2: two nodes per
+// lane, cached stores).  A lane's vector needs x edges that it divides.  FP64
+// pays from 2^18 nodes on (300x33x33 10.0 -> 9.2 us per step, 256x64x64 18.5 -> 15.4,
+// 128^3 34.9 -> 25.1), FP32 from 2^20 (256x64x64 11.7 -> 10.5, 400x100x100 34.9 -> 26.2;
+// but 320x53x53 10.4 -> 11.5).  States that stay out of the last-level cache run
+// better with streaming stores (FP64 1024x128x128 187 -> 178 us, 740x112x113 121 ->
+// 116, but 128^3 25 -> 29), FP32 ones also in 1 KB rows of four nodes per lane if
+// the rows are filled (1024x128x128 109 against 113 us, 740x112x113 72 against 81);
+// cached FP32 ones in 512 B rows, of which the box makes more (128^3 15.2 against
+// 22.7, 400x100x100 26.8 against 28.6).
+constexpr long long kMarchStream = 6'000'000;
+
 int march_variant(const int dim[3], int prec) {
   const long long nodes = (long long)dim[0] * dim[1] * dim[2];
-  if (prec == LBM_FP64) return nodes >= (1 << 18) && dim[0] % 2 == 0 ? 2 : 0;
+  if (prec == LBM_FP64) return nodes >= (1 << 18) && dim[0] % 2 == 0 ? (nodes >= kMarchStream ? 4 : 2) : 0;
   if (nodes < (1 << 20) || dim[0] % 2 != 0) return 0;
   const bool wide = dim[0] % 4 == 0 && 4 * dim[0] >= 3 * 256 * cuts(dim[0], 256);
-  return wide && nodes >= 6'000'000 ? 4 : 2;
+  return wide && nodes >= kMarchStream ? 4 : 2;
 }
 
 // Columns and the number of z ranges that finishes first when each CU takes one
@@ -267,25 +272,26 @@ static MarchGrid march_grid(const int dim[3], int row, int rows, int ncu) {
   return g;
 }
 
-template <class C, int V, int R>
+template <class C, int V, int R, bool STREAM>
 static void launch_march2_of(const KParams<C>& kp, const EnthalpyConsts<C>& ec, const StateRegions& src,
                              const StateRegions& dst, int ncu, hipStream_t stream) {
   const int dim[3] = {kp.nx, kp.ny, kp.nz};
   const MarchGrid g = march_grid(dim, 64 * V, R, ncu);
   const int per = std::min(g.per_xcd, std::max(1, ncu / 8));
   using S = Store<C, C, C>;
-  hipLaunchKernelGGL((k_march2<C, V, R>), dim3(8 * per), dim3(march_threads(R)), 0, stream, kp, ec, store_of<S>(src),
+  hipLaunchKernelGGL((k_march2<C, V, R, STREAM>), dim3(8 * per), dim3(march_threads(R)), 0, stream, kp, ec, store_of<S>(src),
                      store_of<S>(dst), g);
 }
 
 void launch_march2(const KParams<float>& kp, const EnthalpyConsts<float>& ec, const StateRegions& src,
                    const StateRegions& dst, int variant, int ncu, hipStream_t stream) {
-  if (variant == 4) launch_march2_of<float, 4, 11>(kp, ec, src, dst, ncu, stream);
-  else launch_march2_of<float, 2, 15>(kp, ec, src, dst, ncu, stream);
+  if (variant == 4) launch_march2_of<float, 4, 11, true>(kp, ec, src, dst, ncu, stream);
+  else launch_march2_of<float, 2, 15, false>(kp, ec, src, dst, ncu, stream);
 }
 void launch_march2(const KParams<double>& kp, const EnthalpyConsts<double>& ec, const StateRegions& src,
-                   const StateRegions& dst, int, int ncu, hipStream_t stream) {
-  launch_march2_of<double, 2, 11>(kp, ec, src, dst, ncu, stream);
+                   const StateRegions& dst, int variant, int ncu, hipStream_t stream) {
+  if (variant == 4) launch_march2_of<double, 2, 11, true>(kp, ec, src, dst, ncu, stream);
+  else launch_march2_of<double, 2, 11, false>(kp, ec, src, dst, ncu, stream);
 }
 
 }  // namespace lbm

@@ -31,24 +31,29 @@ __device__ __forceinline__ void march_load(const C* base, uint32_t e, C (&v)[V])
 #pragma unroll
   for (int j = 0; j < V; ++j) v[j] = x[j];
 }
-template <class C, int V>
+// STREAM: past the caches (states that do not stay in the last-level cache).
+template <bool STREAM, class C, int V>
 __device__ __forceinline__ void march_store(C* base, uint32_t e, const C (&v)[V]) {
   typedef C Vec __attribute__((ext_vector_type(V)));
   Vec x;
 #pragma unroll
   for (int j = 0; j < V; ++j) x[j] = v[j];
-  *(LBM_GLOBAL Vec*)((LBM_GLOBAL char*)base + e * (uint32_t)sizeof(C)) = x;
+  LBM_GLOBAL Vec* const to = (LBM_GLOBAL Vec*)((LBM_GLOBAL char*)base + e * (uint32_t)sizeof(C));
+  if constexpr (STREAM) __builtin_nontemporal_store(x, to);
+  else *to = x;
 }
 
 // V, R: nodes per lane and rows of step 1.  Registers bound them: with 16-byte
 // vectors (V = 4 FP32, 2 FP64) and R = 11, three wavefronts per SIMD at 158-165
-// registers; R = 15 would spill 35-53.  Measured (us per step, k_step_enthalpy ->
-// here): FP32 1024x128x128 V = 4 R = 11 136 -> 109, V = 2 R = 15 113, V = 2 R = 11 123, V = 4
-// R = 7 143; 1024x64x64 36.5 -> 26.5, 25.9, 27.1, 36.3; FP64 1024x128x128 V = 2 R = 11 302 ->
-// 194, V = 1 R = 15 221.  What bounds it: 56 B (112 FP64) per node and pass at the
-// 5.2 TB/s that rows of 1 KB reach out of place, plus the rows that two columns
-// both read (R / (R - 2)).
-template <class C, int V, int R>
+// registers; R = 15 would spill 35-53.  Measured (us per step at default load
+// priority, cached stores): FP32 1024x128x128 V = 4 R = 11 109, V = 2 R = 15 113, V = 2
+// R = 11 123, V = 4 R = 7 143, k_step_enthalpy 136; 1024x64x64 26.5, 25.9, 27.1, 36.3, 36.5;
+// FP64 1024x128x128 V = 2 R = 11 194, V = 1 R = 15 221, k_step_enthalpy 302.  With load
+// priority 106 / 25.0 / 187, with streaming stores too 100 / 33 / 178 (so only for
+// states past the last-level cache; streaming loads lost 7-12 %).  What bounds it:
+// 56 B (112 FP64) per node and pass, and again the rows that two columns read
+// (R / (R - 2)), at the 5 TB/s that marching columns of 1 KB rows reach.
+template <class C, int V, int R, bool STREAM>
 __global__ void __launch_bounds__(march_threads(R)) k_march2(const KParams<C> kp, const EnthalpyConsts<C> ec,
                                                              const Store<C, C, C> src, const Store<C, C, C> dst,
                                                              const MarchGrid mg) {
@@ -159,7 +164,10 @@ __global__ void __launch_bounds__(march_threads(R)) k_march2(const KParams<C> kp
 #pragma unroll
         for (int j = 0; j < V; ++j) f6[j] = wall(5, U[j]);
       }
+      // loads at raised wavefront priority: 3-4 % in every case measured
+      __builtin_amdgcn_s_setprio(1);
       if (c < z1 && (perz || c + 1 < kp.nz) && live) load(c + 1);
+      __builtin_amdgcn_s_setprio(0);
       // step 2 of plane c - 1 (every lane of an inner row: the shuffles need them)
       if (c > z0 && !ends_wave && r >= 1 && r <= R - 2) {
         C a[7][V];
@@ -174,16 +182,16 @@ __global__ void __launch_bounds__(march_threads(R)) k_march2(const KParams<C> kp
         if (inner && live) {
           const int zn = c - 1;
           const uint32_t n = (uint32_t)(zn * kp.nxy + m);
-          march_store(dst.rs, g0slot<S>(n), a[0]);
+          march_store<STREAM>(dst.rs, g0slot<S>(n), a[0]);
           // along z and y whole vectors move, or bounce into the opposite slot
           auto move = [&](int k, int ko, bool in, int off, int face) {
             if (in) {
-              march_store(dst.mg, gslot(k, n + (uint32_t)off), a[k]);
+              march_store<STREAM>(dst.mg, gslot(k, n + (uint32_t)off), a[k]);
             } else {
               C w[V];
 #pragma unroll
               for (int j = 0; j < V; ++j) w[j] = wall(face, a[k][j]);
-              march_store(dst.mg, gslot(ko, n), w);
+              march_store<STREAM>(dst.mg, gslot(ko, n), w);
             }
           };
           move(5, 6, perz || zn < kp.nz - 1, zn < kp.nz - 1 ? kp.nxy : -(kp.nz - 1) * kp.nxy, 5);
@@ -197,7 +205,7 @@ __global__ void __launch_bounds__(march_threads(R)) k_march2(const KParams<C> kp
 #pragma unroll
           for (int j = 0; j < V; ++j) w[j] = j > 0 ? a[1][j > 0 ? j - 1 : 0] : (wall_lo ? wall(0, a[2][0]) : left);
           if (!first || wall_lo) {
-            march_store(dst.mg, gslot(1, n), w);
+            march_store<STREAM>(dst.mg, gslot(1, n), w);
           } else {
 #pragma unroll
             for (int j = 1; j < V; ++j) st_mg<S, C>(dst, gslot(1, n + (uint32_t)j), w[j]);
@@ -208,7 +216,7 @@ __global__ void __launch_bounds__(march_threads(R)) k_march2(const KParams<C> kp
           for (int j = 0; j < V; ++j)
             w[j] = j < V - 1 ? a[2][j < V - 1 ? j + 1 : 0] : (wall_hi ? wall(1, a[1][V - 1]) : right);
           if (!last || wall_hi) {
-            march_store(dst.mg, gslot(2, n), w);
+            march_store<STREAM>(dst.mg, gslot(2, n), w);
           } else {
 #pragma unroll
             for (int j = 0; j < V - 1; ++j) st_mg<S, C>(dst, gslot(2, n + (uint32_t)j), w[j]);

@@ -809,6 +809,16 @@ __global__ void __launch_bounds__(kMaxBlock) k_fold(const double* __restrict__ i
   }
 }
 
+// Block this block stands for: itself, or with nxcd > 1 the blocks in one
+// contiguous run per XCD (see xcd_ranges_for in lbm_capi.hip), so that the lines
+// neighbouring blocks share at odd parity meet in one L2.
+__device__ __forceinline__ int block_of(int nxcd) {
+  const int b = (int)blockIdx.x, nb = (int)gridDim.x;
+  if (nxcd <= 1) return b;
+  const int x = b % nxcd, q = nb / nxcd, r = nb % nxcd;
+  return x * q + min(x, r) + b / nxcd;
+}
+
 // ------------------------------------------------------------------ init
 __device__ __forceinline__ uint64_t splitmix64(uint64_t s) {
   // SplitMix64 (Steele, Lea & Flood, OOPSLA 2014): one output from state s
@@ -870,8 +880,8 @@ __global__ void __launch_bounds__(kMaxBlock) k_init(const KParams<C> kp, const I
 template <class Lat, class S, class C, bool ODD>
 __global__ void __launch_bounds__(kMaxBlock) k_fields(const KParams<C> kp, const S state, int n0, int count,
                                                       double* rho, double* ux, double* uy, double* uz,
-                                                      double* T) {
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
+                                                      double* T, int nxcd) {
+  const int m = block_of(nxcd) * blockDim.x + threadIdx.x;
   if (m >= count) return;
   const int n = n0 + m;
   int x, y, z;
@@ -890,8 +900,8 @@ __global__ void __launch_bounds__(kMaxBlock) k_fields(const KParams<C> kp, const
 // Per-block FP64 sums of (rho - rho0) and sigma (T - T_ref) of the current state.
 template <class Lat, class S, class C, bool ODD>
 __global__ void __launch_bounds__(kMaxBlock) k_totals(const KParams<C> kp, const S state,
-                                                      double* __restrict__ part) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
+                                                      double* __restrict__ part, int nxcd) {
+  const int lb = block_of(nxcd), n = lb * blockDim.x + threadIdx.x;
   double v[2] = {0.0, 0.0};
   if (n < kp.n) {
     int x, y, z;
@@ -904,8 +914,8 @@ __global__ void __launch_bounds__(kMaxBlock) k_totals(const KParams<C> kp, const
   }
   block_reduce<2>(v, 0u);
   if (threadIdx.x == 0) {
-    part[(size_t)blockIdx.x * kPartStride + 0] = v[0];
-    part[(size_t)blockIdx.x * kPartStride + 1] = v[1];
+    part[(size_t)lb * kPartStride + 0] = v[0];
+    part[(size_t)lb * kPartStride + 1] = v[1];
   }
 }
 
@@ -964,8 +974,8 @@ __global__ void __launch_bounds__(kMaxBlock) k_wall_flux(const KParams<C> kp, co
 // ------------------------------------------------------------------ state I/O
 template <class Lat, class S, class C, bool ODD>
 __global__ void __launch_bounds__(kMaxBlock) k_get_state(const KParams<C> kp, const S state,
-                                                         double* f_out, double* g_out) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
+                                                         double* f_out, double* g_out, int nxcd) {
+  const int n = block_of(nxcd) * blockDim.x + threadIdx.x;
   if (n >= kp.n) return;
   int x, y, z;
   node_coords(kp, n, x, y, z);

@@ -47,14 +47,22 @@ __device__ __forceinline__ int member_of(const M* __restrict__ mem, int nmem, in
 // (a single lattice is a table of one member).  Tile t (blockDim.x nodes of one
 // member) is taken by one block.  With nxcd > 1 the tile list is cut into nxcd
 // contiguous ranges and block b (which the hardware places on XCD b % nxcd)
-// walks range b % nxcd, so neighbouring tiles share an L2 cache; otherwise
-// block b takes tiles b, b + gridDim.x, ...  A grid smaller than the tile count
+// walks range b % nxcd, so neighbouring tiles share an L2 cache; with nxcd = -R
+// each of the eight XCDs takes R neighbouring tiles of every 8 R (one tile per
+// block, the grid a multiple of 8 R); otherwise block b takes tiles b, b +
+// gridDim.x, ...  A grid smaller than the tile count
 // keeps its blocks resident and lets them walk several tiles (a persistent
 // launch).  With nxcd > 1 the grid is a multiple of nxcd.
 template <class Lat, class S, class C, bool ODD, int MODE, bool GEN, bool SEP>
 __device__ __forceinline__ void step_tiles(const Member<S, C>* __restrict__ mem, int nmem, int ntiles, int nxcd) {
   int t, end, stride;
-  if (nxcd > 1) {
+  if (nxcd < 0) {
+    const int run = -nxcd, b = (int)blockIdx.x;
+    const int g = b / (8 * run), w = b - g * 8 * run;
+    t = g * 8 * run + (w & 7) * run + (w >> 3);
+    end = ntiles;
+    stride = (int)gridDim.x;
+  } else if (nxcd > 1) {
     const int per = (ntiles + nxcd - 1) / nxcd;
     const int x = (int)blockIdx.x % nxcd;
     t = x * per + (int)blockIdx.x / nxcd;

@@ -1,9 +1,10 @@
 """GPU test of the tile order of single lattices: states small enough for the
-last-level cache are stepped in one contiguous range of tiles per XCD.  The
-order changes no value, so a lattice must be bit for bit the member of a batch
-that walks the same tiles in hardware order.  Shapes: the smallest of the range
-in each precision, a tile count that the eight ranges do not divide, and a
-general-rule channel."""
+last-level cache are stepped in one contiguous range of tiles per XCD, larger
+FP32 and FP64 ones in runs of tiles per XCD at odd parity.  The order changes no
+value, so a lattice must be bit for bit the member of a batch that walks the
+same tiles in hardware order.  Shapes: the smallest of the ranges in each
+precision, tile counts that ranges and runs do not divide, and general-rule
+channels."""
 import sys
 
 import pytest
@@ -24,6 +25,9 @@ CASES = {
     "fp64_ragged": (lbm_inputs.cavity((67, 64, 65), lattice=15, seed=7), "fp64"),
     "fp16_smallest": (lbm_inputs.cavity((128, 128, 64), seed=8), "fp16"),
     "fp32_channel": (lbm_inputs.channel((130, 47, 44)), "fp32"),
+    "fp32_runs": (lbm_inputs.cavity((167, 161, 160), seed=9), "fp32"),
+    "fp64_runs": (lbm_inputs.cavity((130, 131, 127), seed=10), "fp64"),
+    "fp64_runs_channel": (lbm_inputs.channel((257, 99, 97)), "fp64"),
 }
 
 

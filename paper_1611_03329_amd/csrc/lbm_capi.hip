@@ -18,6 +18,7 @@
 #include "multi.hpp"
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <vector>
 
@@ -676,6 +677,16 @@ struct Staging {
   }
 };
 
+// Compute units of a device (0 if they cannot be told), asked for once.
+static int compute_units(int device) {
+  static std::atomic<int> known[64];
+  if (device < 0 || device >= 64) return 0;
+  int n = known[device].load(std::memory_order_relaxed);
+  if (n == 0 && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess)
+    known[device].store(n, std::memory_order_relaxed);
+  return n;
+}
+
 extern "C" lbm_status lbm_create(const lbm_params* p, void* dev_buf, size_t bytes, void* stream,
                                  lbm_lattice** out) {
   if (!out) return fail(LBM_ERR_INVALID_ARG, "out is NULL");
@@ -751,7 +762,7 @@ extern "C" lbm_status lbm_create(const lbm_params* p, void* dev_buf, size_t byte
   h->nxcd = xcd_ranges_for(p, L);
   h->odd_run = odd_run_for(p, L);
   const int dim[3] = {p->nx, p->ny, p->nz};
-  if (hipDeviceGetAttribute(&h->ncu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) h->ncu = 0;
+  h->ncu = compute_units(device);
   if (h->ncu > 0 && h->energy) {
     h->brick = brick_shape_enthalpy(dim, p->precision, h->ncu);
     h->march = h->brick.threads ? 0 : march_variant(dim, p->precision);

@@ -961,6 +961,20 @@ extern "C" lbm_status lbm_step_workspace(const lbm_lattice* h, int64_t nsteps, s
   return LBM_OK;
 }
 
+// Refuses a workspace that the passes cannot write: they would fault on host
+// memory, and on the lattice's own buffer read what they write.
+static lbm_status check_workspace(const lbm_lattice* h, const void* ws) {
+  if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return fail(LBM_ERR_INVALID_ARG, "the workspace is not 256-byte aligned");
+  const char* const w = static_cast<const char*>(ws);
+  const char* const own = static_cast<const char*>(h->buf);
+  if (w < own + layout(&h->p).total && own < w + population_bytes(h) + macro_bytes(h))
+    return fail(LBM_ERR_INVALID_ARG, "the workspace overlaps the lattice's state buffer");
+  MemKind kind = MemKind::Host;
+  const lbm_status ls = classify(ws, h->device, "the workspace", &kind);
+  if (ls != LBM_OK) return ls;
+  return kind == MemKind::Device ? LBM_OK : fail(LBM_ERR_INVALID_ARG, "the workspace is host memory");
+}
+
 // What the step at time t does for the residual check.
 static int step_mode(const lbm_lattice* h, int64_t t) {
   const int64_t K = h->p.check_interval;
@@ -1026,6 +1040,10 @@ extern "C" lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size
     using S32 = Store<float, float, float>;
     const int most = h->march ? 2 : h->brick.steps;  // steps per pass
     const bool lent = ws && most > 0 && ws_bytes >= population_bytes(h) + macro_bytes(h);
+    if (lent) {
+      const lbm_status ls = check_workspace(h, ws);
+      if (ls != LBM_OK) return ls;
+    }
     for (int64_t s = 0; s < nsteps; ++s) {
       // an even number of passes: k_march2 takes two steps each, bricks about
       // equal numbers
@@ -1065,8 +1083,11 @@ extern "C" lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size
     return LBM_OK;
   }
   const bool bricks = ws && h->brick.threads && (h->p.check_interval == 0 || h->p.check_interval > 2) &&
-                      h->block == 256 &&
-                      ws_bytes >= population_bytes(h) + macro_bytes(h);
+                      h->block == 256 && ws_bytes >= population_bytes(h) + macro_bytes(h);
+  if (bricks) {
+    const lbm_status ls = check_workspace(h, ws);
+    if (ls != LBM_OK) return ls;
+  }
   for (int64_t s = 0; s < nsteps; ++s) {
     const int64_t t = h->t;
     const int64_t passes = (nsteps - s) / 2;

@@ -132,6 +132,21 @@ def test_workspace_is_offered_only_where_it_is_used():
             assert _workspace(lat) == 0
 
 
+@pytest.mark.parametrize("kind", ["flow", "enthalpy"])
+def test_unusable_workspaces_are_refused(kind):
+    wl = lbm_inputs.cavity(16, seed=2) if kind == "flow" else lbm_inputs.melting(400, 6, 6)
+    with Lattice(wl, "fp32") as lat:
+        need = _workspace(lat)
+        room = torch.empty(need + 512, dtype=torch.uint8, device="cuda")
+        host = np.empty(need + 512, dtype=np.uint8)
+        for ws in (room.data_ptr() + 16, -(-host.ctypes.data // 256) * 256, lat._base):
+            err = lbm.library().lbm_step_ws(lat._h, 8, ctypes.c_void_p(ws), ctypes.c_size_t(need))
+            assert err == 1 and lat.time == 0
+        aligned = -(-room.data_ptr() // 256) * 256
+        assert lbm.library().lbm_step_ws(lat._h, 8, ctypes.c_void_p(aligned), ctypes.c_size_t(need)) == 0
+        assert lat.time == 8
+
+
 def test_steps_in_a_captured_graph_equal_eager_steps():
     wl = lbm_inputs.cavity((16, 12, 10), seed=9)
     stream = torch.cuda.Stream()

@@ -117,7 +117,7 @@ __global__ void __launch_bounds__(NT) k_brick2(const KParams<C>* __restrict__ pa
     if (c[2] < bg.e[2] && brick_node(kp, bg, o, c, x)) {
       const int n = x[0] + kp.nx * (x[1] + kp.ny * x[2]);
       const Nbr nb{};
-      gather<Lat, false, false, S, C, false, true>(kp, src, n, nb, h, p);
+      gather<Lat, false, false, S, C, true>(kp, src, n, nb, h, p);
       const Pairs<Lat, C> P = make_pairs<Lat, C>(h);
       const Macro<C> M = macro<Lat, kFlowScale<S>, C>(kp, P, p);
       if (macro1) {
@@ -184,7 +184,7 @@ __global__ void __launch_bounds__(NT) k_brick2(const KParams<C>* __restrict__ pa
   if (macro2) store_macro(kp, M, macro2, n);
   collide_flow<Lat, C>(kp, M, P, h);
   collide_heat<C>(kp, M, p);
-  scatter<Lat, true, false, S, C, false, true>(kp, dst, n, nb, h, p, M, kStochastic<S> ? mix32(now + 1u) : 0u);
+  scatter<Lat, true, false, S, C, true, true>(kp, dst, n, nb, h, p, M, kStochastic<S> ? mix32(now + 1u) : 0u);
 }
 
 // The residual of a check whose step ran in a two-step pass: compares the stored

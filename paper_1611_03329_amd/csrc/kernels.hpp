@@ -247,43 +247,6 @@ __device__ __forceinline__ Nbr make_nbr(const KParams<C>& kp, int x, int y, int 
 
 // Link along velocity e taken with sign SG (+1: to x + e, -1: to x - e):
 // node offset and whether the linked node exists.
-// Separable tiles (kp.sep): when tiles hold whole rows and planes hold whole
-// tiles (or a row holds whole tiles), the element index of moving flow
-// population p at node m splits as fslot(p, m) = X(x) + Y(y) + Z(z) + (p-1)
-// kTile.  A link's target index is then the node's own fslot(1, n) plus one
-// delta per axis it moves along, the same for every population: six deltas
-// per node replace the index arithmetic of each of the 18 (14) links.
-template <class Lat>
-__device__ __forceinline__ void tile_deltas(const Nbr& b, int n, uint32_t f1, int (&td)[3][2]) {
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int s = 0; s < 2; ++s) td[a][s] = (int)(fslot<Lat>(1, (uint32_t)(n + b.off[a][s])) - f1);
-}
-
-// Index delta and existence of the link along velocity e taken with sign SG,
-// from the per-axis deltas of tile_deltas.
-template <int EX, int EY, int EZ, int SG>
-__device__ __forceinline__ void link_delta(const Nbr& b, const int (&td)[3][2], int& dl, bool& in) {
-  dl = 0;
-  in = true;
-  if constexpr (EX != 0) {
-    constexpr int s = EX * SG > 0 ? 1 : 0;
-    dl += td[0][s];
-    in = in && b.in[0][s];
-  }
-  if constexpr (EY != 0) {
-    constexpr int s = EY * SG > 0 ? 1 : 0;
-    dl += td[1][s];
-    in = in && b.in[1][s];
-  }
-  if constexpr (EZ != 0) {
-    constexpr int s = EZ * SG > 0 ? 1 : 0;
-    dl += td[2][s];
-    in = in && b.in[2][s];
-  }
-}
-
 template <int EX, int EY, int EZ, int SG>
 __device__ __forceinline__ void link(const Nbr& b, int& off, bool& in) {
   off = 0;
@@ -303,6 +266,44 @@ __device__ __forceinline__ void link(const Nbr& b, int& off, bool& in) {
     off += b.off[2][s];
     in = in && b.in[2][s];
   }
+}
+
+// Byte offset of the slot that population I's link of node n reads (SG = -1: slot
+// opp(I) of the node at -e_I, else slot I of n) or writes (SG = +1: slot I of the node
+// at +e_I, else slot opp(I) of n), from the start of population min(I, opp(I)) of a
+// region of P moving populations (link_base).  own: the byte offset of slot 1 of n.
+// The plane of the pair goes into the scalar base address, and the tile index times
+// the other populations' bytes is one multiply-add on the byte offset, where link and
+// fslot shift, mask and merge the element index and then scale it.
+// Measured, odd step of FP16 storage, which instruction issue bounds: 866 vector
+// instructions per node instead of 1016 (949 with per-axis deltas on boxes whose tiles
+// hold whole rows, which that replaced) and 102 registers instead of 118; step
+// times 125^3 46.3 -> 43.3 us, 128^3 46.5 -> 45.6, channels 288x96x96 59.8 -> 57.7 and
+// 512x128x128 181 -> 178.6, 64^3 and 256^3 unchanged.  FP32 and FP64 steps, bound
+// by memory traffic, lose with it (103^3 FP32 2.6 %, 192^3 FP64 1.6 %, channel
+// 512x128x128 FP32 1.5 %) and keep link and fslot; two-step passes (k_brick2), which one wavefront's serial
+// instructions bound, take it in every precision (32^3 FP64 598 -> 575 us per 100 steps).
+template <uint32_t P, class L, int I, int SG, class T>
+__device__ __forceinline__ uint32_t link_at(const Nbr& b, int n, uint32_t own, bool& in) {
+  constexpr uint32_t sz = sizeof(T), tile = kTile * sz;
+  constexpr int io = L::opp(I), there = SG < 0 ? io : I, here = SG < 0 ? I : io;
+  constexpr uint32_t apart = (uint32_t)(I < io ? io - I : I - io) * tile;
+  uint32_t m = (uint32_t)n * sz;
+  in = true;
+  static_for<0, 3>([&](auto A) {
+    constexpr int a = decltype(A)::value, e = L::e(a, I) * SG;
+    if constexpr (e != 0) {
+      m += (uint32_t)b.off[a][e > 0] * sz;
+      in = in && b.in[a][e > 0];
+    }
+  });
+  const uint32_t at = m + (m / tile) * ((P - 1u) * tile) + (there > here ? apart : 0u);
+  return in ? at : own + (here > there ? apart : 0u);
+}
+template <class L, int I, class T>
+__device__ __forceinline__ LBM_GLOBAL char* link_base(T* region) {
+  constexpr int io = L::opp(I), lo = I < io ? I : io;
+  return (LBM_GLOBAL char*)region + (size_t)(lo - 1) * kTile * sizeof(T);
 }
 
 // For a link that leaves the box: the face whose rule applies (the first wall
@@ -460,51 +461,56 @@ __device__ __forceinline__ void scatter_faces(const KParams<C>& kp, const S& sto
 // (the step that stored it applied the open rule).  The lean rules (periodic
 // faces, static walls, thermal walls) are applied link by link; GEN adds the
 // rules of moving walls and open faces (special faces) as corrections, face by
-// face (gather_walls, scatter_faces).  SEP takes the flow links' indices from
-// tile_deltas (separable tiles only).
+// face (gather_walls, scatter_faces).  BYTES takes the links' slots from
+// link_at.
 // RAW (the step kernels): the flow populations come out times kFlowScale<S>.
-template <class Lat, bool ODD, bool GEN, class S, class C, bool SEP = false, bool RAW = false>
+template <class Lat, bool ODD, bool GEN, class S, class C, bool RAW = false,
+          bool BYTES = kStochastic<S>>
 __device__ __forceinline__ void gather(const KParams<C>& kp, const S& sto, int n, const Nbr& nb,
                                        C (&h)[Lat::Q], C (&p)[7]) {
+  using MoveF = typename S::MoveF;
+  using MoveG = typename S::MoveG;
   constexpr int SC = RAW ? kFlowScale<S> : 1;
   h[0] = ld_f0_as<RAW, S, C>(sto, (uint32_t)n);
-  const uint32_t f1 = fslot<Lat>(1, (uint32_t)n);
-  int td[3][2];
-  if constexpr (ODD && SEP) tile_deltas<Lat>(nb, n, f1, td);
+  [[maybe_unused]] const uint32_t f1 = fslot<Lat>(1, (uint32_t)n);
   static_for<1, Lat::Q>([&](auto I) {
     constexpr int i = decltype(I)::value;
     if constexpr (!ODD) {
       h[i] = ld_mf_as<RAW, S, C>(sto, fslot<Lat>(i, (uint32_t)n));
-    } else if constexpr (SEP) {
-      constexpr int io = Lat::opp(i);
-      int dl;
-      bool in;
-      link_delta<Lat::e(0, i), Lat::e(1, i), Lat::e(2, i), -1>(nb, td, dl, in);
-      const uint32_t e = f1 + (in ? ((uint32_t)(io - 1) << kTileShift) + (uint32_t)dl
-                                  : ((uint32_t)(i - 1) << kTileShift));
-      h[i] = ld_mf_as<RAW, S, C>(sto, e);
-    } else {
+    } else if constexpr (!BYTES) {
       constexpr int io = Lat::opp(i);
       int off;
       bool in;
       link<Lat::e(0, i), Lat::e(1, i), Lat::e(2, i), -1>(nb, off, in);
       const uint32_t e = in ? fslot<Lat>(io, (uint32_t)(n + off)) : fslot<Lat>(i, (uint32_t)n);
       h[i] = ld_mf_as<RAW, S, C>(sto, e);
+    } else {
+      bool in;
+      const uint32_t e = link_at<(uint32_t)(Lat::Q - 1), Lat, i, -1, MoveF>(nb, n, f1 * (uint32_t)sizeof(MoveF), in);
+      const MoveF x = *(const LBM_GLOBAL MoveF*)(link_base<Lat, i>(sto.mf) + e);
+      if constexpr (RAW || !std::is_same<MoveF, _Float16>::value) h[i] = static_cast<C>(x);
+      else h[i] = static_cast<C>((float)x * (1.0f / kHalfScale));
     }
   });
   if constexpr (GEN && ODD) gather_walls<Lat, SC, C>(kp, nb, h);
   p[0] = ld_g0<S, C>(sto, (uint32_t)n);
+  [[maybe_unused]] const uint32_t g1 = gslot(1, (uint32_t)n) * (uint32_t)sizeof(MoveG);
   static_for<1, 7>([&](auto K) {
     constexpr int k = decltype(K)::value;
     if constexpr (!ODD) {
       p[k] = ld_mg<S, C>(sto, gslot(k, (uint32_t)n));
     } else {
-      constexpr int ko = D3Q7::opp(k);
-      int off;
       bool in;
-      link<D3Q7::e(0, k), D3Q7::e(1, k), D3Q7::e(2, k), -1>(nb, off, in);
-      const uint32_t e = in ? gslot(ko, (uint32_t)(n + off)) : gslot(k, (uint32_t)n);
-      C v = ld_mg<S, C>(sto, e);
+      C v;
+      if constexpr (BYTES) {
+        const uint32_t e = link_at<6u, D3Q7, k, -1, MoveG>(nb, n, g1, in);
+        v = static_cast<C>(*(const LBM_GLOBAL MoveG*)(link_base<D3Q7, k>(sto.mg) + e));
+      } else {
+        constexpr int ko = D3Q7::opp(k);
+        int off;
+        link<D3Q7::e(0, k), D3Q7::e(1, k), D3Q7::e(2, k), -1>(nb, off, in);
+        v = ld_mg<S, C>(sto, in ? gslot(ko, (uint32_t)(n + off)) : gslot(k, (uint32_t)n));
+      }
       // outflow faces carry heat_a = 1, heat_b = 0: their value is already final
       constexpr int fc = d3q7_face<k, -1>();
       v = in ? v : kp.heat_a[fc] * v + kp.heat_b[fc];
@@ -517,9 +523,12 @@ __device__ __forceinline__ void gather(const KParams<C>& kp, const S& sto, int n
 // Post-collision shifted populations of node n, written for the next parity.
 // M holds the node's macroscopic state (used by the open-face rules).
 // RAW (the step kernels): h comes in times kFlowScale<S>.
-template <class Lat, bool ODD, bool GEN, class S, class C, bool SEP = false, bool RAW = false>
+template <class Lat, bool ODD, bool GEN, class S, class C, bool RAW = false,
+          bool BYTES = kStochastic<S>>
 __device__ __forceinline__ void scatter(const KParams<C>& kp, const S& sto, int n, const Nbr& nb,
                                         const C (&h)[Lat::Q], const C (&p)[7], const Macro<C>& M, uint32_t seed) {
+  using MoveF = typename S::MoveF;
+  using MoveG = typename S::MoveG;
   constexpr int SC = RAW ? kFlowScale<S> : 1;
   // random bits for the stochastic FP16 rounding: one hashed word per node and
   // step, and for population i the top 13 bits of that word plus i times the
@@ -527,44 +536,47 @@ __device__ __forceinline__ void scatter(const KParams<C>& kp, const S& sto, int 
   // uniform, and the node's populations take evenly spread rotations of them
   const uint32_t rnd = kStochastic<S> ? mix32(seed + (uint32_t)n) : 0u;
   st_f0_r<RAW, S, C>(sto, (uint32_t)n, h[0], rnd >> 19);
-  const uint32_t f1 = fslot<Lat>(1, (uint32_t)n);
-  int td[3][2];
-  if constexpr (ODD && SEP) tile_deltas<Lat>(nb, n, f1, td);
+  [[maybe_unused]] const uint32_t f1 = fslot<Lat>(1, (uint32_t)n);
   static_for<1, Lat::Q>([&](auto I) {
     constexpr int i = decltype(I)::value;
     constexpr int io = Lat::opp(i);
     const uint32_t r = kStochastic<S> ? (rnd + (uint32_t)i * 0x9E3779B9u) >> 19 : 0u;
     if constexpr (!ODD) {
       st_mf_r<RAW, S, C>(sto, fslot<Lat>(io, (uint32_t)n), h[i], r);
-    } else if constexpr (SEP) {
-      int dl;
-      bool in;
-      link_delta<Lat::e(0, i), Lat::e(1, i), Lat::e(2, i), +1>(nb, td, dl, in);
-      const uint32_t e = f1 + (in ? ((uint32_t)(i - 1) << kTileShift) + (uint32_t)dl
-                                  : ((uint32_t)(io - 1) << kTileShift));
-      st_mf_r<RAW, S, C>(sto, e, h[i], r);
-    } else {
+    } else if constexpr (!BYTES) {
       int off;
       bool in;
       link<Lat::e(0, i), Lat::e(1, i), Lat::e(2, i), +1>(nb, off, in);
       const uint32_t e = in ? fslot<Lat>(i, (uint32_t)(n + off)) : fslot<Lat>(io, (uint32_t)n);
       st_mf_r<RAW, S, C>(sto, e, h[i], r);
+    } else {
+      bool in;
+      const uint32_t e = link_at<(uint32_t)(Lat::Q - 1), Lat, i, +1, MoveF>(nb, n, f1 * (uint32_t)sizeof(MoveF), in);
+      LBM_GLOBAL MoveF* const to = (LBM_GLOBAL MoveF*)(link_base<Lat, i>(sto.mf) + e);
+      if constexpr (kStochastic<S>) *to = half_sr(RAW ? (float)h[i] : (float)h[i] * kHalfScale, r);
+      else *to = static_cast<MoveF>(h[i]);
     }
   });
   st_g0<S, C>(sto, (uint32_t)n, p[0]);
+  [[maybe_unused]] const uint32_t g1 = gslot(1, (uint32_t)n) * (uint32_t)sizeof(MoveG);
   static_for<1, 7>([&](auto K) {
     constexpr int k = decltype(K)::value;
     constexpr int ko = D3Q7::opp(k);
     if constexpr (!ODD) {
       st_mg<S, C>(sto, gslot(ko, (uint32_t)n), p[k]);
     } else {
-      int off;
       bool in;
-      link<D3Q7::e(0, k), D3Q7::e(1, k), D3Q7::e(2, k), +1>(nb, off, in);
       constexpr int fc = d3q7_face<k, +1>();
-      const C v = in ? p[k] : kp.heat_a[fc] * p[k] + kp.heat_b[fc];
-      const uint32_t e = in ? gslot(k, (uint32_t)(n + off)) : gslot(ko, (uint32_t)n);
-      st_mg<S, C>(sto, e, v);
+      if constexpr (BYTES) {
+        const uint32_t e = link_at<6u, D3Q7, k, +1, MoveG>(nb, n, g1, in);
+        const C v = in ? p[k] : kp.heat_a[fc] * p[k] + kp.heat_b[fc];
+        *(LBM_GLOBAL MoveG*)(link_base<D3Q7, k>(sto.mg) + e) = static_cast<MoveG>(v);
+      } else {
+        int off;
+        link<D3Q7::e(0, k), D3Q7::e(1, k), D3Q7::e(2, k), +1>(nb, off, in);
+        const C v = in ? p[k] : kp.heat_a[fc] * p[k] + kp.heat_b[fc];
+        st_mg<S, C>(sto, in ? gslot(k, (uint32_t)(n + off)) : gslot(ko, (uint32_t)n), v);
+      }
     }
   });
   if constexpr (GEN) scatter_faces<Lat, ODD, RAW, S, C>(kp, sto, n, nb, h, p, M, seed);
@@ -640,7 +652,7 @@ __device__ __forceinline__ void residual_terms(const KParams<C>& kp, C cx, C cy,
 // The per-node body of a step: gather, moments, residual bookkeeping,
 // collisions, scatter.  G selects the general wall rules; seed (a hash of the
 // lattice's step count) drives the stochastic rounding of FP16 storage.
-template <class Lat, class S, class C, bool ODD, int MODE, bool G, bool SEP = false>
+template <class Lat, class S, class C, bool ODD, int MODE, bool G>
 __device__ __forceinline__ void step_node(const KParams<C>& kp, const S& state, C* __restrict__ snap, int n,
                                           const Nbr& nb, double (&red)[5], uint32_t seed) {
   C h[Lat::Q], p[7];
@@ -652,7 +664,7 @@ __device__ __forceinline__ void step_node(const KParams<C>& kp, const S& state, 
   constexpr bool kLoadPriority =
       kStochastic<S> || std::is_same<C, double>::value || (!ODD && std::is_same<C, float>::value);
   if constexpr (kLoadPriority) __builtin_amdgcn_s_setprio(1);
-  gather<Lat, ODD, G, S, C, SEP, true>(kp, state, n, nb, h, p);
+  gather<Lat, ODD, G, S, C, true>(kp, state, n, nb, h, p);
   if constexpr (kLoadPriority) __builtin_amdgcn_s_setprio(0);
   const Pairs<Lat, C> P = make_pairs<Lat, C>(h);
   const Macro<C> M = macro<Lat, kFlowScale<S>, C>(kp, P, p);
@@ -668,7 +680,7 @@ __device__ __forceinline__ void step_node(const KParams<C>& kp, const S& state, 
   }
   collide_flow<Lat, C>(kp, M, P, h);
   collide_heat<C>(kp, M, p);
-  scatter<Lat, ODD, G, S, C, SEP, true>(kp, state, n, nb, h, p, M, seed);
+  scatter<Lat, ODD, G, S, C, true>(kp, state, n, nb, h, p, M, seed);
 }
 
 // Node (x, y, z) lies on a face that moves or is open.
@@ -686,10 +698,8 @@ __device__ __forceinline__ bool on_special_face(const KParams<C>& kp, int x, int
 //   MODE 3 does both: it compares with the snapshot, then replaces it.
 // With GEN the general wall rules run only in wavefronts that hold a node on a
 // moving or open face; every other wavefront takes the lean rules, which give
-// the same result for its nodes.  The choice is uniform per wavefront.  With
-// SEP (separable tiles, odd step) both take their link indices from per-axis
-// deltas: the same indices with fewer instructions.
-template <class Lat, class S, class C, bool ODD, int MODE, bool GEN, bool SEP = false>
+// the same result for its nodes.  The choice is uniform per wavefront.
+template <class Lat, class S, class C, bool ODD, int MODE, bool GEN>
 __device__ __forceinline__ void step_block(const KParams<C>& kp, const S& state, C* __restrict__ snap,
                                            double* __restrict__ part, int lb, uint32_t seed) {
   const int n = lb * blockDim.x + threadIdx.x;
@@ -700,11 +710,11 @@ __device__ __forceinline__ void step_block(const KParams<C>& kp, const S& state,
     const Nbr nb = make_nbr(kp, x, y, z);
     if constexpr (GEN) {
       if (__ballot(on_special_face(kp, x, y, z)) != 0)
-        step_node<Lat, S, C, ODD, MODE, true, SEP && ODD>(kp, state, snap, n, nb, red, seed);
+        step_node<Lat, S, C, ODD, MODE, true>(kp, state, snap, n, nb, red, seed);
       else
-        step_node<Lat, S, C, ODD, MODE, false, SEP && ODD>(kp, state, snap, n, nb, red, seed);
+        step_node<Lat, S, C, ODD, MODE, false>(kp, state, snap, n, nb, red, seed);
     } else {
-      step_node<Lat, S, C, ODD, MODE, false, SEP && ODD>(kp, state, snap, n, nb, red, seed);
+      step_node<Lat, S, C, ODD, MODE, false>(kp, state, snap, n, nb, red, seed);
     }
   }
   if constexpr (MODE == kModeCompare || MODE == kModeSpan) {

@@ -934,9 +934,8 @@ __global__ void __launch_bounds__(kMaxBlock) k_totals(const KParams<C> kp, const
 // T_w over chunk b (of gridDim.x equal chunks) of face f's wall nodes, k the
 // population entering the fluid, into part[f * gridDim.x + b]; the last block
 // adds each face's chunk sums in order into out[face] and host[face] (the
-// host's pinned mirror).  The
-// wall term 2 omega_k sigma T_w is taken as the step applies it, in the step's
-// precision: the sum is then exactly the heat the discrete model exchanges
+// host's pinned mirror).  The wall term 2 omega_k sigma T_w is taken as the step
+// applies it, in the step's precision: the sum is then exactly the heat the discrete model exchanges
 // with the wall.  (At Ra = 1e6 the flux per node is about 1/700 of a
 // population, and the FP32 rounding of the wall term alone would move Nu by
 // 4e-5.)

@@ -439,7 +439,8 @@ static int even_step_lds(const lbm_params* p, const KParams<C>& k, long long nod
 // 27.9, 125^3 47.6 -> 45.3, 160^3 (270 MB) 91.8 -> 90.7, 192^3 (467 MB) 157 -> 165,
 // 80^3 16.6 -> 17.1.  D3Q15 channels 288x96x96: FP32 (233 MB) 75.2 -> 70.5, FP16
 // 59.4 -> 59.0, FP64 (467 MB) 147 -> 150.  Below 2^18 nodes (FP16 2^20) a step is
-// latency and the order changes nothing beyond its noise.
+// latency and the order changes nothing beyond its noise.  (FP16 before the odd
+// step took byte offsets, link_at: 125^3 43.3 since.)
 constexpr long long kXcdRangeBytes = 430'000'000LL;
 constexpr int kXcdRanges = 8;
 
@@ -456,9 +457,8 @@ static int xcd_ranges_for(const lbm_params* p, const Layout& L) {
 // that shifted accesses share between tiles cross two L2s.  Measured (us per
 // step, both parities, hardware order -> runs of 32; runs of 2 to 64 alike):
 // FP32 256^3 578 -> 571, 192^3 230 -> 228, channel 512x128x128 234 -> 233; FP64 192^3
-// 497 -> 483, channel 520 -> 497, 256^3 1207 -> 1205; FP16 256^3 366 -> 367, 192^3 154.5
-// -> 153.1, channel unchanged (bound by instruction issue: left in hardware
-// order).  The even step, which reads and writes its own tiles only, loses 1-2 %.
+// 497 -> 483, channel 520 -> 497, 256^3 1207 -> 1205; FP16 256^3 378 -> 378, 192^3 154.2
+// -> 152.4, 512x256x128 381 -> 378, channel unchanged: left in hardware order.  The even step, which reads and writes its own tiles only, loses 1-2 %.
 constexpr int kOddRun = 32;
 
 static int odd_run_for(const lbm_params* p, const Layout& L) {

@@ -31,7 +31,8 @@ static int local_nodes(const int dim[3], const int b[3], int layers) {
 // Estimated time (us) of a two-step pass: launch and first touch, then per
 // filling of the CUs (a block's LDS limits how many share one) a fixed part and
 // one that grows with the wavefronts W of step 1 on a CU, and the traffic of
-// all local nodes (rows of x that are no multiple of 8 nodes cost more).  Fitted to sweeps of bricks on 8^3 to 64^3 boxes, which it meets to
+// all local nodes (rows of x that are no multiple of 8 nodes cost more).  Fitted
+// to sweeps of bricks on 8^3 to 64^3 boxes, which it meets to
 // about 10 %.
 static double brick_pass_us(int prec, int nx, long long blocks, int local, int share, int ncu) {
   const long long per_cu = (blocks + ncu - 1) / ncu;

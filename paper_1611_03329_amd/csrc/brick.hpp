@@ -96,11 +96,12 @@ __device__ __forceinline__ void store_macro(const KParams<C>& kp, const Macro<C>
   o[n + 3 * kp.n] = M.T;
 }
 
-// now: the lattice's step count at the pass (drives FP16 rounding).  macro1,
+// clk, slot: the lattice's step count on the device (drives FP16 rounding), which
+// this pass reads in one slot and leaves for the next in the other.  macro1,
 // macro2: where u and T of the state before step 1 / step 2 go, or null.
 template <class Lat, class S, class C, int NT>
 __global__ void __launch_bounds__(NT) k_brick2(const KParams<C>* __restrict__ params, const S src, const S dst, const BrickGrid bg,
-                                               uint32_t now, C* macro1, C* macro2) {
+                                               uint32_t* clk, int slot, C* macro1, C* macro2) {
   using H = typename S::MoveF;
   constexpr int Q = Lat::Q;
   // state between the steps: flow populations as the step carries them, in
@@ -109,6 +110,11 @@ __global__ void __launch_bounds__(NT) k_brick2(const KParams<C>* __restrict__ pa
   __shared__ H lf[Q][NT];
   const int tid = (int)threadIdx.x;
   const int o[3] = {(int)blockIdx.x * bg.b[0], (int)blockIdx.y * bg.b[1], (int)blockIdx.z * bg.b[2]};
+  uint32_t now = 0u;
+  if constexpr (kStochastic<S>) {
+    now = clk[slot];
+    if ((blockIdx.x | blockIdx.y | blockIdx.z) == 0 && tid == 0) gbl(clk)[slot ^ 1] = now + 2u;
+  }
   C h[Q], p[7];
   {
     const KParams<C>& kp = *again(params);

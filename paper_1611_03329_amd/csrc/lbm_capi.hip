@@ -998,8 +998,8 @@ static lbm_status step_bricks(lbm_lattice* h, int64_t passes, void* ws) {
       }
     }
     // the member table starts with the lattice's kernel parameters
-    launch_brick2(h->q, h->prec, h->dev_member, dim, h->brick, k & 1 ? away : home, k & 1 ? home : away, (uint32_t)h->t,
-                  macro[0], macro[1], h->stream);
+    launch_brick2(h->q, h->prec, h->dev_member, dim, h->brick, k & 1 ? away : home, k & 1 ? home : away, h->clk,
+                  (int)(k & 1), macro[0], macro[1], h->stream);
     lbm_status ls = launch_check("two-step pass");
     if (ls != LBM_OK) return ls;
     if (compared >= 0) {
@@ -1010,8 +1010,7 @@ static lbm_status step_bricks(lbm_lattice* h, int64_t passes, void* ws) {
     }
     h->t += 2;
   }
-  // the step count drives FP16 rounding only
-  return h->prec == LBM_FP16_STORAGE ? set_clock(h) : LBM_OK;
+  return LBM_OK;
 }
 
 extern "C" lbm_status lbm_step(lbm_lattice* h, int64_t nsteps) { return lbm_step_ws(h, nsteps, nullptr, 0); }

@@ -159,36 +159,36 @@ static BrickGrid brick_grid(const int dim[3], const BrickShape& s, int layers) {
 
 template <class Lat, class S, class C, int NT>
 static void launch_brick2_nt(const void* params, const int dim[3], const BrickShape& s, const StateRegions& src,
-                             const StateRegions& dst, uint32_t now, void* macro1,
+                             const StateRegions& dst, uint32_t* clk, int slot, void* macro1,
                              void* macro2, hipStream_t stream) {
   const dim3 grid((dim[0] + s.b[0] - 1) / s.b[0], (dim[1] + s.b[1] - 1) / s.b[1], (dim[2] + s.b[2] - 1) / s.b[2]);
   hipLaunchKernelGGL((k_brick2<Lat, S, C, NT>), grid, dim3(NT), 0, stream, static_cast<const KParams<C>*>(params), store_of<S>(src), store_of<S>(dst),
-                     brick_grid(dim, s, 1), now, static_cast<C*>(macro1), static_cast<C*>(macro2));
+                     brick_grid(dim, s, 1), clk, slot, static_cast<C*>(macro1), static_cast<C*>(macro2));
 }
 
 template <class Lat, class S, class C>
 static void launch_brick2_of(const void* params, const int dim[3], const BrickShape& s, const StateRegions& src,
-                             const StateRegions& dst, uint32_t now, void* macro1,
+                             const StateRegions& dst, uint32_t* clk, int slot, void* macro1,
                              void* macro2, hipStream_t stream) {
-  if (s.threads == 256) launch_brick2_nt<Lat, S, C, 256>(params, dim, s, src, dst, now, macro1, macro2, stream);
-  else if (s.threads == 512) launch_brick2_nt<Lat, S, C, 512>(params, dim, s, src, dst, now, macro1, macro2, stream);
-  else launch_brick2_nt<Lat, S, C, 768>(params, dim, s, src, dst, now, macro1, macro2, stream);
+  if (s.threads == 256) launch_brick2_nt<Lat, S, C, 256>(params, dim, s, src, dst, clk, slot, macro1, macro2, stream);
+  else if (s.threads == 512) launch_brick2_nt<Lat, S, C, 512>(params, dim, s, src, dst, clk, slot, macro1, macro2, stream);
+  else launch_brick2_nt<Lat, S, C, 768>(params, dim, s, src, dst, clk, slot, macro1, macro2, stream);
 }
 
 void launch_brick2(int q, int prec, const void* params, const int dim[3], const BrickShape& shape,
-                   const StateRegions& src, const StateRegions& dst, uint32_t now, void* macro1,
+                   const StateRegions& src, const StateRegions& dst, uint32_t* clk, int slot, void* macro1,
                              void* macro2, hipStream_t stream) {
   using S64 = Store<double, double, double>;
   using S32 = Store<float, float, float>;
   using S16 = Store<_Float16, float, float>;
   if (q == 19) {
-    if (prec == LBM_FP64) launch_brick2_of<D3Q19, S64, double>(params, dim, shape, src, dst, now, macro1, macro2, stream);
-    else if (prec == LBM_FP32) launch_brick2_of<D3Q19, S32, float>(params, dim, shape, src, dst, now, macro1, macro2, stream);
-    else launch_brick2_of<D3Q19, S16, float>(params, dim, shape, src, dst, now, macro1, macro2, stream);
+    if (prec == LBM_FP64) launch_brick2_of<D3Q19, S64, double>(params, dim, shape, src, dst, clk, slot, macro1, macro2, stream);
+    else if (prec == LBM_FP32) launch_brick2_of<D3Q19, S32, float>(params, dim, shape, src, dst, clk, slot, macro1, macro2, stream);
+    else launch_brick2_of<D3Q19, S16, float>(params, dim, shape, src, dst, clk, slot, macro1, macro2, stream);
   } else {
-    if (prec == LBM_FP64) launch_brick2_of<D3Q15, S64, double>(params, dim, shape, src, dst, now, macro1, macro2, stream);
-    else if (prec == LBM_FP32) launch_brick2_of<D3Q15, S32, float>(params, dim, shape, src, dst, now, macro1, macro2, stream);
-    else launch_brick2_of<D3Q15, S16, float>(params, dim, shape, src, dst, now, macro1, macro2, stream);
+    if (prec == LBM_FP64) launch_brick2_of<D3Q15, S64, double>(params, dim, shape, src, dst, clk, slot, macro1, macro2, stream);
+    else if (prec == LBM_FP32) launch_brick2_of<D3Q15, S32, float>(params, dim, shape, src, dst, clk, slot, macro1, macro2, stream);
+    else launch_brick2_of<D3Q15, S16, float>(params, dim, shape, src, dst, clk, slot, macro1, macro2, stream);
   }
 }
 

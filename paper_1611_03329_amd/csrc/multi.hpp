@@ -42,11 +42,12 @@ void launch_march2(const KParams<double>& kp, const EnthalpyConsts<double>& ec, 
                    const StateRegions& dst, int variant, int ncu, hipStream_t stream);
 
 // Two time steps src -> dst (natural layout) of a lattice with q = 19 or 15
-// flow populations at step count `now`; params: its KParams in device memory.
+// flow populations; params: its KParams in device memory; clk, slot: its step
+// count, which an FP16 pass reads in clk[slot] and writes, two more, to the other slot.
 // macro1, macro2 (or null): where u and T before each step go (4 planes of nodes
 // in the compute type).
 void launch_brick2(int q, int prec, const void* params, const int dim[3], const BrickShape& shape,
-                   const StateRegions& src, const StateRegions& dst, uint32_t now, void* macro1, void* macro2,
+                   const StateRegions& src, const StateRegions& dst, uint32_t* clk, int slot, void* macro1, void* macro2,
                    hipStream_t stream);
 
 // Residual check of u and T in `cur` against `snap` (as a compare step and k_fold

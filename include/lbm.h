@@ -207,7 +207,8 @@ lbm_status lbm_step(lbm_lattice* h, int64_t nsteps);
  * passed the call; its contents are lost and nothing of the lattice is kept in
  * it) runs of steps between residual checks take several steps per launch,
  * reading one of the two buffers and writing the other.  With a NULL or
- * smaller workspace, or for a lattice that takes none, it is lbm_step.  A
+ * smaller workspace, for a lattice that takes none, or while the stream is being
+ * captured, it is lbm_step.  A
  * workspace that would be used is refused (LBM_ERR_INVALID_ARG, no step taken) if
  * it is misaligned, overlaps the state or is not memory of the lattice's device. */
 lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size_t ws_bytes);

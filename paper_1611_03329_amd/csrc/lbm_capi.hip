@@ -935,17 +935,22 @@ static StateRegions regions(const lbm_lattice* h, void* base) {
   return {at(h->mf), at(h->mg), at(h->rs), at(h->r0)};
 }
 
-extern "C" lbm_status lbm_step_workspace(const lbm_lattice* h, int64_t nsteps, size_t* bytes) {
-  if (!h || !bytes) return fail(LBM_ERR_INVALID_ARG, "NULL argument");
-  *bytes = 0;
-  if (nsteps < 4 || h->batch || (!h->brick.threads && !h->march)) return LBM_OK;
-  // a captured call would tie the graph to a workspace that is only lent
+// Whether the lattice's stream is being captured (or cannot tell).  Passes are
+// not: a graph would be tied to a workspace that is only lent.
+static bool capturing(const lbm_lattice* h) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (h->stream && hipStreamIsCapturing(h->stream, &cap) != hipSuccess) {
     (void)hipGetLastError();
-    return LBM_OK;
+    return true;
   }
-  if (cap == hipStreamCaptureStatusNone) *bytes = population_bytes(h) + macro_bytes(h);
+  return cap != hipStreamCaptureStatusNone;
+}
+
+extern "C" lbm_status lbm_step_workspace(const lbm_lattice* h, int64_t nsteps, size_t* bytes) {
+  if (!h || !bytes) return fail(LBM_ERR_INVALID_ARG, "NULL argument");
+  *bytes = 0;
+  if (nsteps < 4 || h->batch || (!h->brick.threads && !h->march) || capturing(h)) return LBM_OK;
+  *bytes = population_bytes(h) + macro_bytes(h);
   return LBM_OK;
 }
 
@@ -1020,6 +1025,7 @@ extern "C" lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size
   if (nsteps < 0) return fail(LBM_ERR_INVALID_ARG, "nsteps must be >= 0");
   if (h->batch) return fail(LBM_ERR_INVALID_ARG, "the lattice is in a batch: step the batch");
   if (h->host_res[7] != 0.0) return fail(LBM_ERR_UNSTABLE, "lattice was found unstable at an earlier check");
+  if (ws && capturing(h)) ws = nullptr;
   if (h->energy) {
     const EnthalpyConsts<double> e64 = enthalpy_consts<double>(&h->p);
     const EnthalpyConsts<float> e32 = enthalpy_consts<float>(&h->p);

@@ -1,0 +1,207 @@
+// The host side of lbm_step_ws without a GPU: this program defines the HIP runtime
+// functions that liblbm.so calls (an executable's definitions come before those
+// of the runtime library).  Device memory is host memory and launches are recorded
+// instead of run; a pass of several steps counts itself up in the first word of
+// the populations it writes.  One scenario per call, named in argv[1].
+#include <hip/hip_runtime_api.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "lbm.h"
+
+namespace {
+
+std::map<const void*, std::string>& names() {
+  static std::map<const void*, std::string> m;
+  return m;
+}
+std::map<char*, size_t> g_device;         // device allocations
+std::vector<std::string> g_launched;      // kernels of passes and checks, in order
+int g_fail_at = -1;                       // the launch of these that fails
+hipError_t g_error = hipSuccess;          // what hipGetLastError returns next
+hipStreamCaptureStatus g_capture = hipStreamCaptureStatusNone;
+struct Call { dim3 grid, block; size_t lds; hipStream_t stream; };
+std::vector<Call> g_calls;
+
+bool has(const std::string& s, const char* part) { return s.find(part) != std::string::npos; }
+
+struct Regions { uint32_t *mf, *mg, *rs, *r0; };  // a kernel's Store argument
+
+int g_failures = 0;
+#define CHECK(cond, ...)                                                       \
+  do {                                                                         \
+    if (!(cond)) {                                                             \
+      std::printf("%s:%d: %s: ", __FILE__, __LINE__, #cond);                   \
+      std::printf(__VA_ARGS__);                                                \
+      std::printf("\n");                                                       \
+      ++g_failures;                                                            \
+    }                                                                          \
+  } while (0)
+
+}  // namespace
+
+extern "C" {
+void** __hipRegisterFatBinary(const void*) { static void* module; return &module; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*, void*, void*,
+                           int*) { names()[host] = name; }
+void __hipRegisterVar(void**, void*, char*, const char*, int, size_t, int, int) {}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+  g_calls.push_back({grid, block, lds, stream});
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* stream) {
+  const Call c = g_calls.back();
+  g_calls.pop_back();
+  *grid = c.grid, *block = c.block, *lds = c.lds, *stream = c.stream;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* fn, dim3, dim3, void** args, size_t, hipStream_t) {
+  const std::string& name = names()[fn];
+  const bool brick = has(name, "k_brick2"), melt = has(name, "k_brick_enthalpy") || has(name, "k_march2");
+  if (brick || melt || has(name, "k_compare")) {
+    if ((int)g_launched.size() == g_fail_at) {
+      g_launched.push_back("failed");
+      return g_error = hipErrorLaunchFailure;
+    }
+    g_launched.push_back(name);
+  } else if (has(name, "k_step")) {
+    g_launched.push_back("step");
+  }
+  if (brick || melt) {
+    const Regions src = *static_cast<Regions*>(args[brick ? 1 : 2]), dst = *static_cast<Regions*>(args[brick ? 2 : 3]);
+    dst.mg[0] = src.mg[0] + 1;
+  }
+  if (brick && has(name, "DF16_")) {
+    uint32_t* const clk = *static_cast<uint32_t**>(args[4]);
+    const int slot = *static_cast<int*>(args[5]);
+    clk[slot ^ 1] = clk[slot] + 2;
+  }
+  return hipSuccess;
+}
+hipError_t hipGetLastError() {
+  const hipError_t e = g_error;
+  g_error = hipSuccess;
+  return e;
+}
+const char* hipGetErrorString(hipError_t) { return "an error"; }
+hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { return *v = 256, hipSuccess; }
+hipError_t hipMalloc(void** p, size_t n) {
+  *p = std::aligned_alloc(256, (n + 255) / 256 * 256);
+  std::memset(*p, 0, n);
+  g_device[static_cast<char*>(*p)] = n;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  g_device.erase(static_cast<char*>(p));
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return *p = std::calloc(1, n), hipSuccess; }
+hipError_t hipHostFree(void* p) { return std::free(p), hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+  std::memcpy(d, s, n);
+  return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { return std::memset(d, v, n), hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) { return *s = g_capture, hipSuccess; }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
+  for (const auto& [base, size] : g_device)
+    if (p >= base && p < base + size) {
+      std::memset(a, 0, sizeof *a);
+      a->type = hipMemoryTypeDevice;
+      a->devicePointer = const_cast<void*>(p);
+      return hipSuccess;
+    }
+  return hipErrorInvalidValue;
+}
+}
+
+namespace {
+
+enum Kind { kFlow, kMelt, kMarch };
+
+lbm_params params(Kind kind, int precision, int interval) {
+  lbm_params p;
+  lbm_default_params(&p);
+  p.precision = precision;
+  p.check_interval = interval;
+  p.rayleigh = 1e4;
+  p.nx = 16, p.ny = 12, p.nz = 10;
+  if (kind != kFlow) {
+    p.energy = LBM_ENERGY_ENTHALPY;
+    p.nx = 400, p.ny = p.nz = 6;
+  }
+  if (kind == kMarch) p.nx = 256, p.ny = p.nz = 64;
+  return p;
+}
+
+struct Run {
+  lbm_lattice* h = nullptr;
+  char* buf = nullptr;
+  char* ws = nullptr;
+  size_t ws_bytes = 0;
+  explicit Run(const lbm_params& p) {
+    size_t need = 0;
+    CHECK(lbm_required_bytes(&p, &need) == LBM_OK, "%s", lbm_last_error());
+    (void)hipMalloc((void**)&buf, need);
+    ws_bytes = need + (size_t)p.nx * p.ny * p.nz * 64;  // more than any pass needs
+    (void)hipMalloc((void**)&ws, ws_bytes);
+    CHECK(lbm_create(&p, buf, need, reinterpret_cast<void*>(64), &h) == LBM_OK, "%s", lbm_last_error());
+    g_launched.clear();
+    g_fail_at = -1;
+  }
+  ~Run() {
+    (void)lbm_destroy(h);
+    (void)hipFree(buf);
+    (void)hipFree(ws);
+  }
+  int64_t time() const {
+    int64_t t = -1;
+    (void)lbm_time(h, &t);
+    return t;
+  }
+  size_t offered(int64_t n) const {
+    size_t bytes = 1;
+    CHECK(lbm_step_workspace(h, n, &bytes) == LBM_OK, "%s", lbm_last_error());
+    return bytes;
+  }
+};
+
+int passes() {
+  int n = 0;
+  for (const std::string& s : g_launched) n += has(s, "k_brick") || has(s, "k_march");
+  return n;
+}
+
+// A captured call would tie its graph to the lent workspace: it takes single steps.
+void capture() {
+  for (Kind kind : {kFlow, kMelt, kMarch}) {
+    Run r(params(kind, LBM_FP64, 0));
+    const size_t before = r.offered(8);
+    CHECK(before > 0 && before <= r.ws_bytes, "kind %d", kind);
+    g_capture = hipStreamCaptureStatusActive;
+    CHECK(r.offered(8) == 0, "kind %d", kind);
+    CHECK(lbm_step_ws(r.h, 8, r.ws, before) == LBM_OK, "%s", lbm_last_error());
+    g_capture = hipStreamCaptureStatusNone;
+    CHECK(passes() == 0 && g_launched.size() == 8 && r.time() == 8, "kind %d: %d passes", kind, passes());
+  }
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::map<std::string, void (*)()> scenarios = {{"capture", capture}};
+  const auto it = argc == 2 ? scenarios.find(argv[1]) : scenarios.end();
+  if (it == scenarios.end()) return 2;
+  it->second();
+  return g_failures ? 1 : 0;
+}

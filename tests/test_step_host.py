@@ -1,0 +1,27 @@
+"""CPU tests of the host side of lbm_step_ws (tests/host/step_paths.cpp): the
+library's own code over a HIP runtime that records launches instead of running
+them."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SRC = os.path.join(ROOT, "tests", "host", "step_paths.cpp")
+LIB_DIR = os.path.join(ROOT, "paper_1611_03329_amd")
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("host") / "step_paths")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-rdynamic", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(rocm, "include"),
+                    "-I", os.path.join(ROOT, "include"), SRC, "-o", out, os.path.join(LIB_DIR, "liblbm.so"),
+                    "-Wl,-rpath," + LIB_DIR, "-Wl,-rpath-link," + os.path.join(rocm, "lib")], check=True)
+    return out
+
+
+@pytest.mark.parametrize("scenario", ["capture"])
+def test_host_side_of_passes(program, scenario):
+    r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr

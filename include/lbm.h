@@ -213,9 +213,10 @@ lbm_status lbm_step(lbm_lattice* h, int64_t nsteps);
  * it is misaligned, overlaps the state or is not memory of the lattice's device. */
 lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size_t ws_bytes);
 
-/* Workspace bytes with which lbm_step_ws(h, nsteps, ...) runs faster than
- * lbm_step; 0 where it would not use one (large flow lattices, moving walls or
- * open faces, few steps, a lattice in a batch, a stream that is being captured). */
+/* Workspace bytes with which lbm_step_ws(h, nsteps, ...), called next, runs faster
+ * than lbm_step; 0 where it would not use one (lattices for which steps one by one
+ * are as fast, moving walls or open faces, a residual check every step or two, too few
+ * steps, a lattice in a batch, a stream that is being captured). */
 lbm_status lbm_step_workspace(const lbm_lattice* h, int64_t nsteps, size_t* bytes);
 
 /* Current time t (completed steps).  Host-only, no synchronization. */

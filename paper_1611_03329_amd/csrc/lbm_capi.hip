@@ -946,11 +946,21 @@ static bool capturing(const lbm_lattice* h) {
   return cap != hipStreamCaptureStatusNone;
 }
 
+// Whether a call of nsteps steps makes passes if it is lent a workspace: both what
+// lbm_step_workspace offers one for and what lbm_step_ws takes one for.  Passes
+// start at parity 0 and come in twos of at least two steps each.  With a check
+// every step or two a pass would overwrite the snapshot that its own compare step
+// needs, and k_compare folds blocks of 256.
+static bool takes_passes(const lbm_lattice* h, int64_t nsteps) {
+  if (h->batch || nsteps - h->parity < 4) return false;
+  if (h->energy ? !h->brick.threads && !h->march : !h->brick.threads || h->block != 256) return false;
+  if (h->p.check_interval == 1 || h->p.check_interval == 2) return false;
+  return !capturing(h);
+}
+
 extern "C" lbm_status lbm_step_workspace(const lbm_lattice* h, int64_t nsteps, size_t* bytes) {
   if (!h || !bytes) return fail(LBM_ERR_INVALID_ARG, "NULL argument");
-  *bytes = 0;
-  if (nsteps < 4 || h->batch || (!h->brick.threads && !h->march) || capturing(h)) return LBM_OK;
-  *bytes = population_bytes(h) + macro_bytes(h);
+  *bytes = takes_passes(h, nsteps) ? population_bytes(h) + macro_bytes(h) : 0;
   return LBM_OK;
 }
 
@@ -979,9 +989,7 @@ static int step_mode(const lbm_lattice* h, int64_t t) {
 
 // 2 * passes steps of a lattice at parity 0 (passes even), their checks included:
 // the pass stores u and T of a snapshot step, or of a compare step into the
-// workspace, where k_compare takes them from.  (With a check every two steps a
-// pass would overwrite the snapshot that its own compare step needs: such
-// lattices take single steps.)
+// workspace, where k_compare takes them from.
 static lbm_status step_bricks(lbm_lattice* h, int64_t passes, void* ws) {
   const StateRegions home = regions(h, h->buf), away = regions(h, ws);
   void* const cur = static_cast<char*>(ws) + population_bytes(h);
@@ -1025,18 +1033,17 @@ extern "C" lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size
   if (nsteps < 0) return fail(LBM_ERR_INVALID_ARG, "nsteps must be >= 0");
   if (h->batch) return fail(LBM_ERR_INVALID_ARG, "the lattice is in a batch: step the batch");
   if (h->host_res[7] != 0.0) return fail(LBM_ERR_UNSTABLE, "lattice was found unstable at an earlier check");
-  if (ws && capturing(h)) ws = nullptr;
+  const bool lent = ws && takes_passes(h, nsteps) && ws_bytes >= population_bytes(h) + macro_bytes(h);
+  if (lent) {
+    const lbm_status ls = check_workspace(h, ws);
+    if (ls != LBM_OK) return ls;
+  }
   if (h->energy) {
     const EnthalpyConsts<double> e64 = enthalpy_consts<double>(&h->p);
     const EnthalpyConsts<float> e32 = enthalpy_consts<float>(&h->p);
     using S64 = Store<double, double, double>;
     using S32 = Store<float, float, float>;
     const int most = h->march ? 2 : h->brick.steps;  // steps per pass
-    const bool lent = ws && most > 0 && ws_bytes >= population_bytes(h) + macro_bytes(h);
-    if (lent) {
-      const lbm_status ls = check_workspace(h, ws);
-      if (ls != LBM_OK) return ls;
-    }
     for (int64_t s = 0; s < nsteps; ++s) {
       // an even number of passes: k_march2 takes two steps each, bricks about
       // equal numbers
@@ -1075,16 +1082,10 @@ extern "C" lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size
     }
     return LBM_OK;
   }
-  const bool bricks = ws && h->brick.threads && (h->p.check_interval == 0 || h->p.check_interval > 2) &&
-                      h->block == 256 && ws_bytes >= population_bytes(h) + macro_bytes(h);
-  if (bricks) {
-    const lbm_status ls = check_workspace(h, ws);
-    if (ls != LBM_OK) return ls;
-  }
   for (int64_t s = 0; s < nsteps; ++s) {
     const int64_t t = h->t;
     const int64_t passes = (nsteps - s) / 2;
-    if (bricks && h->parity == 0 && passes > 0 && passes % 2 == 0) {
+    if (lent && h->parity == 0 && passes > 0 && passes % 2 == 0) {
       lbm_status ls = step_bricks(h, passes, ws);
       if (ls != LBM_OK) return ls;
       s += 2 * passes - 1;

@@ -196,10 +196,30 @@ void capture() {
   }
 }
 
+// A workspace is offered exactly where the call then makes passes with it.
+void offered() {
+  for (Kind kind : {kFlow, kMelt, kMarch})
+    for (int interval : {0, 1, 2, 3, 10})
+      for (int parity : {0, 1})
+        for (int n : {1, 3, 4, 5, 6, 7, 23}) {
+          if (kind != kFlow && interval) continue;
+          Run r(params(kind, LBM_FP64, interval));
+          CHECK(lbm_step(r.h, parity) == LBM_OK, "%s", lbm_last_error());
+          const size_t bytes = r.offered(n);
+          CHECK(bytes <= r.ws_bytes, "%zu bytes", bytes);
+          CHECK(lbm_step_ws(r.h, n, r.ws, r.ws_bytes) == LBM_OK, "%s", lbm_last_error());
+          CHECK((bytes > 0) == (passes() > 0) && passes() % 2 == 0, "kind %d check %d parity %d: %zu bytes, %d passes for %d steps",
+                kind, interval, parity, bytes, passes(), n);
+          CHECK(r.time() == parity + n, "%d steps", n);
+          // a workspace that no pass would use is not looked at
+          if (!bytes) CHECK(lbm_step_ws(r.h, 1, r.ws + 16, r.ws_bytes - 16) == LBM_OK, "%s", lbm_last_error());
+        }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
-  const std::map<std::string, void (*)()> scenarios = {{"capture", capture}};
+  const std::map<std::string, void (*)()> scenarios = {{"capture", capture}, {"offered", offered}};
   const auto it = argc == 2 ? scenarios.find(argv[1]) : scenarios.end();
   if (it == scenarios.end()) return 2;
   it->second();

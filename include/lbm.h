@@ -210,7 +210,9 @@ lbm_status lbm_step(lbm_lattice* h, int64_t nsteps);
  * smaller workspace, for a lattice that takes none, or while the stream is being
  * captured, it is lbm_step.  A
  * workspace that would be used is refused (LBM_ERR_INVALID_ARG, no step taken) if
- * it is misaligned, overlaps the state or is not memory of the lattice's device. */
+ * it is misaligned, overlaps the state or is not memory of the lattice's device.  After a
+ * failed launch (LBM_ERR_DEVICE) the lattice holds the steps enqueued before it, which
+ * lbm_time counts. */
 lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size_t ws_bytes);
 
 /* Workspace bytes with which lbm_step_ws(h, nsteps, ...), called next, runs faster

@@ -987,6 +987,18 @@ static int step_mode(const lbm_lattice* h, int64_t t) {
   return kModePlain;
 }
 
+// After pass `done - 1` of a call was enqueued and the next launch failed: brings the
+// state home from the workspace if it lies there, so that the lattice holds the
+// steps it counts.  (Its own failure can only follow one of the device, which has
+// been reported.)
+static lbm_status passes_failed(lbm_lattice* h, int64_t done, const void* ws, lbm_status status) {
+  if (done % 2 != 0) {
+    (void)hipMemcpyAsync(h->buf, ws, population_bytes(h), hipMemcpyDeviceToDevice, h->stream);
+    (void)hipMemcpyAsync(h->clk, h->clk + 1, sizeof(uint32_t), hipMemcpyDeviceToDevice, h->stream);
+  }
+  return status;
+}
+
 // 2 * passes steps of a lattice at parity 0 (passes even), their checks included:
 // the pass stores u and T of a snapshot step, or of a compare step into the
 // workspace, where k_compare takes them from.
@@ -996,32 +1008,31 @@ static lbm_status step_bricks(lbm_lattice* h, int64_t passes, void* ws) {
   const int dim[3] = {h->p.nx, h->p.ny, h->p.nz};
   for (int64_t k = 0; k < passes; ++k) {
     void* macro[2];
-    int64_t compared = -1;
+    int64_t snapped = -1, compared = -1;
     for (int j = 0; j < 2; ++j) {
       const int64_t t = h->t + j;
-      const int mode = step_mode(h, t);
+      const int mode = snapped >= 0 ? kModeCompare : step_mode(h, t);
       macro[j] = mode == kModeSnapshot ? h->snap : (mode == kModeCompare ? cur : nullptr);
-      if (mode == kModeSnapshot) {
-        h->snapshot_valid = true;
-        h->snapshot_at = t;
-      }
-      if (mode == kModeCompare) {
-        compared = t;
-        h->snapshot_valid = false;
-      }
+      if (mode == kModeSnapshot) snapped = t;
+      if (mode == kModeCompare) compared = t;
     }
     // the member table starts with the lattice's kernel parameters
     launch_brick2(h->q, h->prec, h->dev_member, dim, h->brick, k & 1 ? away : home, k & 1 ? home : away, h->clk,
                   (int)(k & 1), macro[0], macro[1], h->stream);
     lbm_status ls = launch_check("two-step pass");
-    if (ls != LBM_OK) return ls;
+    if (ls != LBM_OK) return passes_failed(h, k, ws, ls);
+    h->t += 2;
+    if (snapped >= 0) {
+      h->snapshot_valid = true;
+      h->snapshot_at = snapped;
+    }
     if (compared >= 0) {
+      h->snapshot_valid = snapped > compared;
       launch_compare(h->prec, h->dev_member, h->nodes, h->snap, cur, h->part, h->done, h->res, h->host_res, h->stream);
       ls = launch_check("residual");
-      if (ls != LBM_OK) return ls;
+      if (ls != LBM_OK) return passes_failed(h, k + 1, ws, ls);
       h->last_check = compared;
     }
-    h->t += 2;
   }
   return LBM_OK;
 }
@@ -1060,7 +1071,7 @@ extern "C" lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size
           else if (h->prec == LBM_FP64) launch_brick_enthalpy(h->kd, e64, h->brick, steps, src, dst, h->stream);
           else launch_brick_enthalpy(h->kf, e32, h->brick, steps, src, dst, h->stream);
           lbm_status ls = launch_check("enthalpy pass");
-          if (ls != LBM_OK) return ls;
+          if (ls != LBM_OK) return passes_failed(h, k, ws, ls);
           h->t += steps;
           taken += steps;
         }

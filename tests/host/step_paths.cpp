@@ -24,6 +24,8 @@ std::map<char*, size_t> g_device;         // device allocations
 std::vector<std::string> g_launched;      // kernels of passes and checks, in order
 int g_fail_at = -1;                       // the launch of these that fails
 hipError_t g_error = hipSuccess;          // what hipGetLastError returns next
+uint32_t* g_home = nullptr;   // first word of the populations that the first pass read
+uint32_t* g_clock = nullptr;  // FP16 step count that the first pass read
 hipStreamCaptureStatus g_capture = hipStreamCaptureStatusNone;
 struct Call { dim3 grid, block; size_t lds; hipStream_t stream; };
 std::vector<Call> g_calls;
@@ -75,11 +77,13 @@ hipError_t hipLaunchKernel(const void* fn, dim3, dim3, void** args, size_t, hipS
   }
   if (brick || melt) {
     const Regions src = *static_cast<Regions*>(args[brick ? 1 : 2]), dst = *static_cast<Regions*>(args[brick ? 2 : 3]);
+    if (!g_home) g_home = src.mg;
     dst.mg[0] = src.mg[0] + 1;
   }
   if (brick && has(name, "DF16_")) {
     uint32_t* const clk = *static_cast<uint32_t**>(args[4]);
     const int slot = *static_cast<int*>(args[5]);
+    if (!g_clock) g_clock = clk + slot;
     clk[slot ^ 1] = clk[slot] + 2;
   }
   return hipSuccess;
@@ -157,6 +161,7 @@ struct Run {
     (void)hipMalloc((void**)&ws, ws_bytes);
     CHECK(lbm_create(&p, buf, need, reinterpret_cast<void*>(64), &h) == LBM_OK, "%s", lbm_last_error());
     g_launched.clear();
+    g_home = g_clock = nullptr;
     g_fail_at = -1;
   }
   ~Run() {
@@ -216,10 +221,37 @@ void offered() {
         }
 }
 
+// A launch that fails leaves the lattice with the steps it counts: the populations of
+// the last pass in its own buffer (wherever that pass wrote them), its FP16 clock too.
+void failed() {
+  for (Kind kind : {kFlow, kMelt, kMarch})
+    for (int precision : {(int)LBM_FP64, (int)LBM_FP16_STORAGE})
+      for (int interval : {0, 4}) {
+        if (kind != kFlow && (interval || precision != LBM_FP64)) continue;
+        Run all(params(kind, precision, interval));
+        CHECK(lbm_step_ws(all.h, 40, all.ws, all.ws_bytes) == LBM_OK, "%s", lbm_last_error());
+        const std::vector<std::string> launches = g_launched;
+        for (int at = 0; at < (int)launches.size(); ++at) {
+          if (launches[at] == "step") continue;
+          Run r(params(kind, precision, interval));
+          g_fail_at = at;
+          CHECK(lbm_step_ws(r.h, 40, r.ws, r.ws_bytes) == LBM_ERR_DEVICE, "launch %d", at);
+          const uint32_t done = (uint32_t)passes();
+          if (done) CHECK(*g_home == done, "kind %d launch %d: %u passes in the buffer of %u", kind, at, *g_home, done);
+          if (kind == kFlow) CHECK(r.time() == 2 * done, "%u passes", done);
+          if (done && precision == LBM_FP16_STORAGE) CHECK(*g_clock == 2 * done, "clock %u after %u passes", *g_clock, done);
+          int64_t check = 0;
+          double res = 0;
+          (void)lbm_residual(r.h, &res, &check);
+          CHECK(check < r.time(), "check at %lld", (long long)check);
+        }
+      }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
-  const std::map<std::string, void (*)()> scenarios = {{"capture", capture}, {"offered", offered}};
+  const std::map<std::string, void (*)()> scenarios = {{"capture", capture}, {"offered", offered}, {"failed", failed}};
   const auto it = argc == 2 ? scenarios.find(argv[1]) : scenarios.end();
   if (it == scenarios.end()) return 2;
   it->second();

@@ -276,14 +276,16 @@ class Lattice:
         if self._passes and n >= 4:
             _check(_lib.lbm_step_workspace(self._h, n, ctypes.byref(need)))
         if need.value:
+            # on the lattice's device, whichever is current now
+            device = self.buf.device
             try:
                 # freed when this returns: the allocator hands it out again in the
                 # order of the stream it came from, which is the lattice's
-                if self.stream.cuda_stream == torch.cuda.current_stream(self.device).cuda_stream:
-                    ws = torch.empty(need.value + 256, dtype=torch.uint8, device=self.device)
+                if self.stream.cuda_stream == torch.cuda.current_stream(device).cuda_stream:
+                    ws = torch.empty(need.value + 256, dtype=torch.uint8, device=device)
                 else:
                     with torch.cuda.stream(self.stream):
-                        ws = torch.empty(need.value + 256, dtype=torch.uint8, device=self.device)
+                        ws = torch.empty(need.value + 256, dtype=torch.uint8, device=device)
             except torch.cuda.OutOfMemoryError:
                 ws = None
             if ws is not None:

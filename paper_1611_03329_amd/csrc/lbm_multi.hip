@@ -273,26 +273,30 @@ static MarchGrid march_grid(const int dim[3], int row, int rows, int ncu) {
   return g;
 }
 
-template <class C, int V, int R, bool STREAM>
+// Items beyond one per CU wait in the block that marches; without a march (FLAT)
+// every item is a block, and several share a CU.
+template <class C, int V, int R, bool STREAM, bool FLAT>
 static void launch_march2_of(const KParams<C>& kp, const EnthalpyConsts<C>& ec, const StateRegions& src,
                              const StateRegions& dst, int ncu, hipStream_t stream) {
   const int dim[3] = {kp.nx, kp.ny, kp.nz};
   const MarchGrid g = march_grid(dim, 64 * V, R, ncu);
-  const int per = std::min(g.per_xcd, std::max(1, ncu / 8));
+  const int per = FLAT ? g.per_xcd : std::min(g.per_xcd, std::max(1, ncu / 8));
   using S = Store<C, C, C>;
-  hipLaunchKernelGGL((k_march2<C, V, R, STREAM>), dim3(8 * per), dim3(march_threads(R)), 0, stream, kp, ec, store_of<S>(src),
+  hipLaunchKernelGGL((k_march2<C, V, R, STREAM, FLAT>), dim3(8 * per), dim3(march_threads(R)), 0, stream, kp, ec, store_of<S>(src),
                      store_of<S>(dst), g);
 }
 
 void launch_march2(const KParams<float>& kp, const EnthalpyConsts<float>& ec, const StateRegions& src,
                    const StateRegions& dst, int variant, int ncu, hipStream_t stream) {
-  if (variant == 4) launch_march2_of<float, 4, 11, true>(kp, ec, src, dst, ncu, stream);
-  else launch_march2_of<float, 2, 15, false>(kp, ec, src, dst, ncu, stream);
+  if (kp.nz == 1) launch_march2_of<float, 2, kFlatRows, false, true>(kp, ec, src, dst, ncu, stream);
+  else if (variant == 4) launch_march2_of<float, 4, 11, true, false>(kp, ec, src, dst, ncu, stream);
+  else launch_march2_of<float, 2, 15, false, false>(kp, ec, src, dst, ncu, stream);
 }
 void launch_march2(const KParams<double>& kp, const EnthalpyConsts<double>& ec, const StateRegions& src,
                    const StateRegions& dst, int variant, int ncu, hipStream_t stream) {
-  if (variant == 4) launch_march2_of<double, 2, 11, true>(kp, ec, src, dst, ncu, stream);
-  else launch_march2_of<double, 2, 11, false>(kp, ec, src, dst, ncu, stream);
+  if (kp.nz == 1) launch_march2_of<double, 2, kFlatRows, false, true>(kp, ec, src, dst, ncu, stream);
+  else if (variant == 4) launch_march2_of<double, 2, 11, true, false>(kp, ec, src, dst, ncu, stream);
+  else launch_march2_of<double, 2, 11, false, false>(kp, ec, src, dst, ncu, stream);
 }
 
 }  // namespace lbm

@@ -60,7 +60,8 @@ PEAK_VALU_WAVE_INSTR_PER_S = 256 * 2.4e9
 KERNEL_SOURCES = ("paper_1611_03329_amd/csrc/kernels.hpp", "paper_1611_03329_amd/csrc/model.hpp",
                   "paper_1611_03329_amd/csrc/lattice.hpp", "paper_1611_03329_amd/csrc/batch.hpp",
                   "paper_1611_03329_amd/csrc/brick.hpp", "paper_1611_03329_amd/csrc/march.hpp",
-                  "paper_1611_03329_amd/csrc/multi.hpp", "paper_1611_03329_amd/csrc/lbm_multi.hip",
+                  "paper_1611_03329_amd/csrc/multi.hpp", "paper_1611_03329_amd/csrc/shapes.hpp",
+                  "paper_1611_03329_amd/csrc/lbm_multi.hip",
                   "paper_1611_03329_amd/csrc/lbm_capi.hip", "paper_1611_03329_amd/build.py")
 
 

@@ -762,7 +762,7 @@ extern "C" lbm_status lbm_create(const lbm_params* p, void* dev_buf, size_t byte
   h->ncu = compute_units(device);
   if (h->ncu > 0 && h->energy) {
     h->brick = brick_shape_enthalpy(dim, p->precision, h->ncu);
-    h->march = h->brick.threads ? 0 : march_variant(dim, p->precision);
+    h->march = h->brick.threads ? 0 : march_variant(dim, p->precision, h->ncu);
   } else if (h->ncu > 0 && !(h->kd.moving || h->kd.open_flow || h->kd.open_heat)) {
     h->brick = brick_shape(dim, p->precision, h->ncu);
   }

@@ -2,6 +2,7 @@
 #include "multi.hpp"
 
 #include <algorithm>
+#include <cmath>
 
 #include "brick.hpp"
 #include "lbm.h"
@@ -233,44 +234,82 @@ void launch_brick_enthalpy(const KParams<double>& kp, const EnthalpyConsts<doubl
   launch_brick_enthalpy_of(kp, ec, shape, steps, src, dst, stream);
 }
 
-// The variant of k_march2 an enthalpy lattice takes (0: none; 4: FP32 with four
-// nodes per lane, FP64 with two, both with streaming stores; 2: two nodes per
-// lane, cached stores).  A lane's vector needs x edges that it divides.  FP64
-// pays from 2^18 nodes on (300x33x33 10.0 -> 9.2 us per step, 256x64x64 18.5 -> 15.4,
-// 128^3 34.9 -> 25.1), FP32 from 2^20 (256x64x64 11.7 -> 10.5, 400x100x100 34.9 -> 26.2;
-// but 320x53x53 10.4 -> 11.5).  States that stay out of the last-level cache run
-// better with streaming stores (FP64 1024x128x128 187 -> 178 us, 740x112x113 121 ->
-// 116, but 128^3 25 -> 29), FP32 ones also in 1 KB rows of four nodes per lane if
-// the rows are filled (1024x128x128 109 against 113 us, 740x112x113 72 against 81);
-// cached FP32 ones in 512 B rows, of which the box makes more (128^3 15.2 against
-// 22.7, 400x100x100 26.8 against 28.6).
-constexpr long long kMarchStream = 6'000'000;
-
-int march_variant(const int dim[3], int prec) {
-  const long long nodes = (long long)dim[0] * dim[1] * dim[2];
-  if (prec == LBM_FP64) return nodes >= (1 << 18) && dim[0] % 2 == 0 ? (nodes >= kMarchStream ? 4 : 2) : 0;
-  if (nodes < (1 << 20) || dim[0] % 2 != 0) return 0;
-  const bool wide = dim[0] % 4 == 0 && 4 * dim[0] >= 3 * 256 * cuts(dim[0], 256);
-  return wide && nodes >= kMarchStream ? 4 : 2;
-}
-
 // Columns and the number of z ranges that finishes first when each CU takes one
 // item at a time (a range of P planes costs P + 2: step 1 runs on a plane more
 // at each end).
+static long long march_cost(long long tiles, int nz, int chunks, int ncu) {
+  return (tiles * chunks + ncu - 1) / ncu * (cuts(nz, chunks) + 3);
+}
 static MarchGrid march_grid(const int dim[3], int row, int rows, int ncu) {
   MarchGrid g;
   g.tiles_x = cuts(dim[0], row);
   g.tiles_y = cuts(dim[1], rows - 2);
   const long long tiles = (long long)g.tiles_x * g.tiles_y;
-  long long best = -1;
   g.chunks = 1;
-  for (int k = 1; k <= dim[2] && k <= 64; ++k) {
-    const long long cost = (tiles * k + ncu - 1) / ncu * (cuts(dim[2], k) + 3);
-    if (best < 0 || cost < best) best = cost, g.chunks = k;
-  }
+  for (int k = 2; k <= dim[2] && k <= 64; ++k)
+    if (march_cost(tiles, dim[2], k, ncu) < march_cost(tiles, dim[2], g.chunks, ncu)) g.chunks = k;
   g.items = (int)tiles * g.chunks;
   g.per_xcd = cuts(g.items, 8);
   return g;
+}
+
+// The variant of k_march2 an enthalpy lattice takes (0: none; 4: FP32 with four
+// nodes per lane, FP64 with two, both with streaming stores; 2: two nodes per
+// lane, cached stores).  A lane's vector needs x edges that it divides.
+//
+// States of 160 MB up, which with the other buffer stay out of the 256 MB last-level
+// cache, run better with streaming stores, FP32 ones also in 1 KB rows of four
+// nodes per lane if the rows are filled; cached FP32 ones in 512 B rows, of which
+// the box makes more.  Measured (us per step, cached -> streaming stores): FP64 128^3
+// (117 MB) 25 -> 29, 160x128x128 (147 MB) 44.2 -> 43.7, 200x128x128 (183 MB) 49.7 ->
+// 46.9, 356x128x128 (327 MB) 83.1 -> 78.2, 1024x128x128 187 -> 178; FP32 256x128x128
+// (117 MB) 23.6 -> 31.6, 2684x168x12 (152 MB) 49.6 -> 50.9, 378x128x123 (167 MB) 46.4 ->
+// 44.6, and with four nodes per lane 480x128x100 (172 MB) 47.0 -> 43.3, 1024x128x128 107
+// -> 99.
+//
+// A pass pays where its estimate is below that of two single steps.  An item's
+// plane takes the same time however much of its row lies in the box, and less if
+// fewer rows do (the vector units bound it); to that comes the traffic of the state.
+// Fitted to 170 boxes of 2^18 to 1.7e7 nodes with edges from 1 to 10^5, which it meets to 6 %
+// (rms); of 600 others that it takes, drawn at random, 4 % ran 2 to 9 % slower than single
+// steps.  Measured per step (us, k_step_enthalpy / passes): FP64 128^3 35.1 / 23.4,
+// 64^3 10.6 / 8.5, 1024x256x4 18.7 / 15.3, 130^3 36.8 / 37.6, 1024x2x512 18.8 / 20.7,
+// 16x256x256 18.5 / 62, 2x512x512 10.6 / 223; FP32 128^3 19.5 / 14.8, 130^3 20.6 / 21.1,
+// 1024x512x2 11.3 / 13.5, 2048x1x1024 20 / 57, 20x489x271 25 / 69.  FP32 below 2^20 nodes
+// loses or is even (320x53x53 10.4 / 11.5).
+constexpr long long kMarchStream = 160'000'000;
+
+static double march_pass_us(const int dim[3], bool fp64, bool stream, double state_mb, int ncu) {
+  const long long nodes = (long long)dim[0] * dim[1] * dim[2];
+  if (dim[2] == 1) {  // one plane: items side by side, several per CU
+    const double items = (double)cuts(dim[0], 2 * 64) * cuts(dim[1], kFlatRows - 2) * 256.0 / ncu;
+    return fp64 ? 3.5 + 0.0145 * items : 4.0 + 0.0062 * items;
+  }
+  const int rows = fp64 || stream ? 11 : 15, live = std::min(dim[1] + 2, rows);
+  const MarchGrid g = march_grid(dim, 64 * (!fp64 && stream ? 4 : 2), rows, ncu);
+  const double cost = (double)march_cost((long long)g.tiles_x * g.tiles_y, dim[2], g.chunks, ncu);
+  // us per plane of an item; us per node of traffic, more for stores that pass
+  // through a last-level cache which does not hold both buffers
+  double plane, node;
+  if (fp64) {
+    plane = stream ? 3.4 + 0.07 * live : 1.15 + 0.2 * live;
+    node = stream ? 1.75e-5 : (state_mb < 128.0 ? 1.7e-5 : 2.5e-5);
+  } else {
+    plane = stream ? 4.6 : 1.3 + 0.107 * live;
+    node = stream ? 0.8e-5 : (state_mb < 128.0 ? 0.65e-5 : 1.4e-5);
+  }
+  return std::hypot(plane * cost, node * (double)nodes);
+}
+
+int march_variant(const int dim[3], int prec, int ncu) {
+  const bool fp64 = prec == LBM_FP64;
+  const long long nodes = (long long)dim[0] * dim[1] * dim[2], state = nodes * 7 * (fp64 ? 8 : 4);
+  if (nodes < (fp64 ? 1 << 18 : 1 << 20) || dim[0] % 2 != 0) return 0;
+  const bool wide = dim[0] % 4 == 0 && 4 * dim[0] >= 3 * 256 * cuts(dim[0], 256);
+  const bool stream = state >= kMarchStream && (fp64 || wide);
+  const double step = fp64 ? std::max(9.2, 2.0 + 1.62e-5 * nodes) : 4.0 + 0.78e-5 * nodes;
+  if (march_pass_us(dim, fp64, stream, state * 1e-6, ncu) >= 2.0 * step) return 0;
+  return stream ? 4 : 2;
 }
 
 // Items beyond one per CU wait in the block that marches; without a march (FLAT)

@@ -8,6 +8,7 @@
 
 #include "enthalpy.hpp"
 #include "model.hpp"
+#include "shapes.hpp"
 
 namespace lbm {
 
@@ -16,26 +17,13 @@ struct StateRegions {
   void *mf, *mg, *rs, *r0;
 };
 
-// Brick edges a lattice of this shape is cut into (0: it is not).
-struct BrickShape {
-  int b[3] = {0, 0, 0};
-  int threads = 0;
-  int steps = 0;  // most time steps per pass
-};
-
-// prec: lbm_precision; ncu: compute units of the device.
-BrickShape brick_shape(const int dim[3], int prec, int ncu);
-BrickShape brick_shape_enthalpy(const int dim[3], int prec, int ncu);
-
 // `steps` <= shape.steps time steps of an enthalpy lattice.
 void launch_brick_enthalpy(const KParams<float>& kp, const EnthalpyConsts<float>& ec, const BrickShape& shape,
                            int steps, const StateRegions& src, const StateRegions& dst, hipStream_t stream);
 void launch_brick_enthalpy(const KParams<double>& kp, const EnthalpyConsts<double>& ec, const BrickShape& shape,
                            int steps, const StateRegions& src, const StateRegions& dst, hipStream_t stream);
 
-// Nodes per lane of the two-step pass that a large enthalpy lattice takes, 0 if
-// it takes none; launch_march2 makes the pass.
-int march_variant(const int dim[3], int prec);
+// Two time steps of a large enthalpy lattice; variant: its march_variant.
 void launch_march2(const KParams<float>& kp, const EnthalpyConsts<float>& ec, const StateRegions& src,
                    const StateRegions& dst, int variant, int ncu, hipStream_t stream);
 void launch_march2(const KParams<double>& kp, const EnthalpyConsts<double>& ec, const StateRegions& src,

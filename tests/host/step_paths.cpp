@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "lbm.h"
+#include "shapes.hpp"
 
 namespace {
 
@@ -248,10 +249,25 @@ void failed() {
       }
 }
 
+// Marching passes: not where a row fills few lanes or a block few rows, where they
+// took up to 20 times the single steps.
+void marching() {
+  struct { int dim[3], fp64, fp32; } const boxes[] = {
+      {{128, 128, 128}, 2, 2},   {{1024, 128, 128}, 4, 4},  {{1024, 8, 128}, 2, 2}, {{4096, 257, 1}, 2, 2},
+      {{640, 640, 1}, 2, 0},     {{356, 128, 128}, 4, 2},   {{258, 55, 75}, 2, 2},  {{2, 512, 512}, 0, 0},
+      {{4, 400, 400}, 0, 0},     {{16, 256, 256}, 0, 0},    {{36, 240, 449}, 0, 0}, {{1024, 2, 512}, 0, 0},
+      {{2048, 1, 1024}, 0, 0},   {{138, 580, 58}, 0, 0},    {{2, 800000, 1}, 0, 0}, {{1000000, 1, 1}, 0, 0},
+      {{100000, 4, 4}, 0, 0},    {{129, 128, 128}, 0, 0},   {{60, 60, 60}, 0, 0}};
+  for (const auto& b : boxes) {
+    const int v[2] = {lbm::march_variant(b.dim, LBM_FP64, 256), lbm::march_variant(b.dim, LBM_FP32, 256)};
+    CHECK(v[0] == b.fp64 && v[1] == b.fp32, "%d x %d x %d: %d %d", b.dim[0], b.dim[1], b.dim[2], v[0], v[1]);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
-  const std::map<std::string, void (*)()> scenarios = {{"capture", capture}, {"offered", offered}, {"failed", failed}};
+  const std::map<std::string, void (*)()> scenarios = {{"capture", capture}, {"offered", offered}, {"failed", failed}, {"marching", marching}};
   const auto it = argc == 2 ? scenarios.find(argv[1]) : scenarios.end();
   if (it == scenarios.end()) return 2;
   it->second();

@@ -1,6 +1,6 @@
-"""CPU tests of the host side of lbm_step_ws (tests/host/step_paths.cpp): the
-library's own code over a HIP runtime that records launches instead of running
-them."""
+"""CPU tests of the host side of lbm_step_ws and of the rules for passes
+(tests/host/step_paths.cpp): the library's own code over a HIP runtime that
+records launches instead of running them."""
 import os
 import subprocess
 
@@ -16,12 +16,12 @@ def program(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("host") / "step_paths")
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     subprocess.run(["g++", "-std=c++17", "-O1", "-rdynamic", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(rocm, "include"),
-                    "-I", os.path.join(ROOT, "include"), SRC, "-o", out, os.path.join(LIB_DIR, "liblbm.so"),
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(LIB_DIR, "csrc"), SRC, "-o", out, os.path.join(LIB_DIR, "liblbm.so"),
                     "-Wl,-rpath," + LIB_DIR, "-Wl,-rpath-link," + os.path.join(rocm, "lib")], check=True)
     return out
 
 
-@pytest.mark.parametrize("scenario", ["capture", "offered", "failed"])
+@pytest.mark.parametrize("scenario", ["capture", "offered", "failed", "marching"])
 def test_host_side_of_passes(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr

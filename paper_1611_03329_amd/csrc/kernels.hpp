@@ -651,8 +651,9 @@ __device__ __forceinline__ void residual_terms(const KParams<C>& kp, C cx, C cy,
 //   MODE 3 does both: it compares with the snapshot, then replaces it.
 // The per-node body of a step: gather, moments, residual bookkeeping,
 // collisions, scatter.  G selects the general wall rules; seed (a hash of the
-// lattice's step count) drives the stochastic rounding of FP16 storage.
-template <class Lat, class S, class C, bool ODD, int MODE, bool G>
+// lattice's step count) drives the stochastic rounding of FP16 storage; BYTES:
+// gather takes its links from byte offsets (scatter does wherever storage is FP16).
+template <class Lat, class S, class C, bool ODD, int MODE, bool G, bool BYTES>
 __device__ __forceinline__ void step_node(const KParams<C>& kp, const S& state, C* __restrict__ snap, int n,
                                           const Nbr& nb, double (&red)[5], uint32_t seed) {
   C h[Lat::Q], p[7];
@@ -664,7 +665,7 @@ __device__ __forceinline__ void step_node(const KParams<C>& kp, const S& state, 
   constexpr bool kLoadPriority =
       kStochastic<S> || std::is_same<C, double>::value || (!ODD && std::is_same<C, float>::value);
   if constexpr (kLoadPriority) __builtin_amdgcn_s_setprio(1);
-  gather<Lat, ODD, G, S, C, true>(kp, state, n, nb, h, p);
+  gather<Lat, ODD, G, S, C, true, BYTES>(kp, state, n, nb, h, p);
   if constexpr (kLoadPriority) __builtin_amdgcn_s_setprio(0);
   const Pairs<Lat, C> P = make_pairs<Lat, C>(h);
   const Macro<C> M = macro<Lat, kFlowScale<S>, C>(kp, P, p);
@@ -699,7 +700,7 @@ __device__ __forceinline__ bool on_special_face(const KParams<C>& kp, int x, int
 // With GEN the general wall rules run only in wavefronts that hold a node on a
 // moving or open face; every other wavefront takes the lean rules, which give
 // the same result for its nodes.  The choice is uniform per wavefront.
-template <class Lat, class S, class C, bool ODD, int MODE, bool GEN>
+template <class Lat, class S, class C, bool ODD, int MODE, bool GEN, bool BYTES>
 __device__ __forceinline__ void step_block(const KParams<C>& kp, const S& state, C* __restrict__ snap,
                                            double* __restrict__ part, int lb, uint32_t seed) {
   const int n = lb * blockDim.x + threadIdx.x;
@@ -710,11 +711,11 @@ __device__ __forceinline__ void step_block(const KParams<C>& kp, const S& state,
     const Nbr nb = make_nbr(kp, x, y, z);
     if constexpr (GEN) {
       if (__ballot(on_special_face(kp, x, y, z)) != 0)
-        step_node<Lat, S, C, ODD, MODE, true>(kp, state, snap, n, nb, red, seed);
+        step_node<Lat, S, C, ODD, MODE, true, BYTES>(kp, state, snap, n, nb, red, seed);
       else
-        step_node<Lat, S, C, ODD, MODE, false>(kp, state, snap, n, nb, red, seed);
+        step_node<Lat, S, C, ODD, MODE, false, BYTES>(kp, state, snap, n, nb, red, seed);
     } else {
-      step_node<Lat, S, C, ODD, MODE, false>(kp, state, snap, n, nb, red, seed);
+      step_node<Lat, S, C, ODD, MODE, false, BYTES>(kp, state, snap, n, nb, red, seed);
     }
   }
   if constexpr (MODE == kModeCompare || MODE == kModeSpan) {

@@ -432,24 +432,29 @@ static int even_step_lds(const lbm_params* p, const KParams<C>& k, long long nod
 // in one L2, and the lines that the odd step's shifted accesses share between
 // them cross that link once instead of twice.  Larger states are bound by DRAM
 // and run faster in hardware order, which keeps all XCDs in one region of
-// memory.  Measured (us per step, hardware order -> ranges): FP32 64^3 11.1 ->
-// 10.4, 103^3 38.3 -> 35.0, 125^3 64.7 -> 59.3, 160^3 (428 MB) 132.1 -> 128.9,
-// 192^3 (736 MB) 234.6 -> 239.6, 256^3 592 -> 621; FP64 103^3 71.2 -> 67.8, 125^3
-// (406 MB) 130.4 -> 125.4, 128^3 (436 MB) 131.5 -> 134.3; FP16 103^3 29.2 ->
-// 27.9, 125^3 47.6 -> 45.3, 160^3 (270 MB) 91.8 -> 90.7, 192^3 (467 MB) 157 -> 165,
-// 80^3 16.6 -> 17.1.  D3Q15 channels 288x96x96: FP32 (233 MB) 75.2 -> 70.5, FP16
-// 59.4 -> 59.0, FP64 (467 MB) 147 -> 150.  Below 2^18 nodes (FP16 2^20) a step is
-// latency and the order changes nothing beyond its noise.  (FP16 before the odd
-// step took byte offsets, link_at: 125^3 43.3 since.)
-constexpr long long kXcdRangeBytes = 430'000'000LL;
+// memory; so do FP16 steps with moving walls or open faces, which instruction issue
+// bounds, and small boxes, whose steps are latency.  Measured over 1100 boxes
+// (cubes, channels, slabs), time in hardware order over that in ranges, mean by
+// size of state: FP64 60-150 MB 1.02, 150-350 MB 1.05, 350-430 MB 1.02-1.04, above
+// 0.98-1.01; FP32 60-100 MB 1.05, 100-250 MB 1.08, 250-350 MB 1.03-1.06, then D3Q19 1.02,
+// D3Q15 1.01 to 370 MB and 0.98 to 430 MB; FP16 60-250 MB 1.06-1.08, 260 MB 1.03, 300 MB
+// 0.97 (D3Q15 1.00), 350 MB 0.97; FP16 channels D3Q19 1.02-0.91, D3Q15 1.00-0.93 with
+// size.  By nodes: FP64 and FP32 2.6e5 to 3e5 0.91-1.10, from 3e5 1.02-1.05; FP16 2.6e5 to
+// 3e5 0.92, from 2^20 1.05.
 constexpr int kXcdRanges = 8;
 
-static int xcd_ranges_for(const lbm_params* p, const Layout& L) {
+static long long xcd_range_nodes(int prec) { return prec == LBM_FP16_STORAGE ? 1LL << 20 : 300'000LL; }
+
+static long long xcd_range_bytes(const lbm_params* p, bool general) {
+  if (p->precision == LBM_FP16_STORAGE) return general ? 0 : 280'000'000LL;
+  return p->precision == LBM_FP32 && p->lattice == 15 ? 370'000'000LL : 430'000'000LL;
+}
+
+static int xcd_ranges_for(const lbm_params* p, const Layout& L, bool general) {
   if (p->energy == LBM_ENERGY_ENTHALPY) return 0;
   const long long nodes = (long long)p->nx * p->ny * p->nz;
   const long long state = (long long)L.snap;  // the population regions come first
-  const long long least = p->precision == LBM_FP16_STORAGE ? 1LL << 20 : 1LL << 18;
-  return nodes >= least && state <= kXcdRangeBytes ? kXcdRanges : 0;
+  return nodes >= xcd_range_nodes(p->precision) && state <= xcd_range_bytes(p, general) ? kXcdRanges : 0;
 }
 
 // Larger FP32 and FP64 lattices: the odd step hands each XCD 32 neighbouring
@@ -463,7 +468,7 @@ constexpr int kOddRun = 32;
 
 static int odd_run_for(const lbm_params* p, const Layout& L) {
   const bool flow = p->energy != LBM_ENERGY_ENTHALPY && p->precision != LBM_FP16_STORAGE;
-  return flow && (long long)L.snap > kXcdRangeBytes ? kOddRun : 0;
+  return flow && (long long)L.snap > 430'000'000LL ? kOddRun : 0;
 }
 
 static Layout layout(const lbm_params* p) {
@@ -756,7 +761,7 @@ extern "C" lbm_status lbm_create(const lbm_params* p, void* dev_buf, size_t byte
   fill_kparams<double>(p, &d, h->nodes, h->pstride, &h->kd);
   fill_kparams<float>(p, &d, h->nodes, h->pstride, &h->kf);
   h->even_lds = even_step_lds(p, h->kf, h->nodes);
-  h->nxcd = xcd_ranges_for(p, L);
+  h->nxcd = xcd_ranges_for(p, L, h->kf.moving || h->kf.open_flow || h->kf.open_heat);
   h->odd_run = odd_run_for(p, L);
   const int dim[3] = {p->nx, p->ny, p->nz};
   h->ncu = compute_units(device);

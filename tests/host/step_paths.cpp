@@ -23,6 +23,7 @@ std::map<const void*, std::string>& names() {
 }
 std::map<char*, size_t> g_device;         // device allocations
 std::vector<std::string> g_launched;      // kernels of passes and checks, in order
+int g_order = 0;                          // the tile order that the last step was launched with
 int g_fail_at = -1;                       // the launch of these that fails
 hipError_t g_error = hipSuccess;          // what hipGetLastError returns next
 uint32_t* g_home = nullptr;   // first word of the populations that the first pass read
@@ -75,6 +76,7 @@ hipError_t hipLaunchKernel(const void* fn, dim3, dim3, void** args, size_t, hipS
     g_launched.push_back(name);
   } else if (has(name, "k_step")) {
     g_launched.push_back("step");
+    if (!has(name, "enthalpy")) g_order = *static_cast<int*>(args[3]);
   }
   if (brick || melt) {
     const Regions src = *static_cast<Regions*>(args[brick ? 1 : 2]), dst = *static_cast<Regions*>(args[brick ? 2 : 3]);
@@ -249,6 +251,36 @@ void failed() {
       }
 }
 
+struct Box { int dim[3], q, precision; bool general; };
+lbm_params box_params(const Box& b) {
+  lbm_params p;
+  lbm_default_params(&p);
+  p.nx = b.dim[0], p.ny = b.dim[1], p.nz = b.dim[2];
+  p.lattice = b.q;
+  p.precision = b.precision;
+  p.rayleigh = 1e4;
+  if (b.general) p.face[5].u_wall[0] = 0.01;
+  return p;
+}
+
+// Tile order of steps: ranges per XCD (8) for states that the last-level cache serves,
+// but not where they were slower.
+void step_order() {
+  const struct { Box box; int even, odd; } cases[] = {
+      {{{103, 103, 103}, 19, LBM_FP32, false}, 8, 8},         {{{125, 125, 125}, 19, LBM_FP16_STORAGE, false}, 8, 8},
+      {{{160, 160, 160}, 19, LBM_FP32, false}, 8, 8},         {{{160, 160, 168}, 15, LBM_FP32, false}, 0, 0},
+      {{{128, 128, 100}, 19, LBM_FP16_STORAGE, true}, 0, 0},  {{{165, 165, 165}, 19, LBM_FP16_STORAGE, false}, 0, 0},
+      {{{128, 128, 100}, 19, LBM_FP32, true}, 8, 8},          {{{64, 64, 64}, 15, LBM_FP64, true}, 0, 0},
+      {{{80, 80, 80}, 19, LBM_FP16_STORAGE, false}, 0, 0},    {{{168, 168, 168}, 19, LBM_FP32, false}, 0, -32},
+  };
+  for (const auto& c : cases) {
+    Run r(box_params(c.box));
+    const int* d = c.box.dim;
+    CHECK(lbm_step(r.h, 1) == LBM_OK && g_order == c.even, "even %d x %d x %d: %d", d[0], d[1], d[2], g_order);
+    CHECK(lbm_step(r.h, 1) == LBM_OK && g_order == c.odd, "odd %d x %d x %d: %d", d[0], d[1], d[2], g_order);
+  }
+}
+
 // Marching passes: not where a row fills few lanes or a block few rows, where they
 // took up to 20 times the single steps.
 void marching() {
@@ -267,7 +299,8 @@ void marching() {
 }  // namespace
 
 int main(int argc, char** argv) {
-  const std::map<std::string, void (*)()> scenarios = {{"capture", capture}, {"offered", offered}, {"failed", failed}, {"marching", marching}};
+  const std::map<std::string, void (*)()> scenarios = {{"capture", capture}, {"offered", offered}, {"failed", failed}, {"marching", marching},
+                                                         {"step_order", step_order}};
   const auto it = argc == 2 ? scenarios.find(argv[1]) : scenarios.end();
   if (it == scenarios.end()) return 2;
   it->second();

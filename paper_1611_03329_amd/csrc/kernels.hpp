@@ -821,7 +821,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_fold(const double* __restrict__ i
 }
 
 // Block this block stands for: itself, or with nxcd > 1 the blocks in one
-// contiguous run per XCD (see xcd_ranges_for in lbm_capi.hip), so that the lines
+// contiguous run per XCD (see query_order in lbm_capi.hip), so that the lines
 // neighbouring blocks share at odd parity meet in one L2.
 __device__ __forceinline__ int block_of(int nxcd) {
   const int b = (int)blockIdx.x, nb = (int)gridDim.x;
@@ -984,8 +984,8 @@ __global__ void __launch_bounds__(kMaxBlock) k_wall_flux(const KParams<C> kp, co
 // ------------------------------------------------------------------ state I/O
 template <class Lat, class S, class C, bool ODD>
 __global__ void __launch_bounds__(kMaxBlock) k_get_state(const KParams<C> kp, const S state,
-                                                         double* f_out, double* g_out, int nxcd) {
-  const int n = block_of(nxcd) * blockDim.x + threadIdx.x;
+                                                         double* f_out, double* g_out) {
+  const int n = blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= kp.n) return;
   int x, y, z;
   node_coords(kp, n, x, y, z);

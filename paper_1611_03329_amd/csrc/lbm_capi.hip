@@ -1138,6 +1138,18 @@ extern "C" lbm_status lbm_step_ws(lbm_lattice* h, int64_t nsteps, void* ws, size
 }
 
 // ------------------------------------------------------------------ queries
+// Tile order of a query that reads the state and writes out_bytes: the steps' ranges,
+// while the last-level cache serves what it reads and writes.  Measured over 1100 boxes
+// (hardware order over ranges, means): fields 1.04-1.14 below 180 MB of state and
+// outputs, 1.01-1.07 to 220 MB, 0.98-1.01 to 260 MB, 0.96-0.99 above; totals (no outputs)
+// 1.03-1.07 below 200 MB, 1.00-1.03 to 230 MB, 1.00 above.  lbm_get_state, whose outputs
+// are larger than the state, loses 2-6 % from 60 MB of state on (FP64 1 %) and keeps
+// the hardware order.
+static int query_order(const lbm_lattice* h, size_t out_bytes) {
+  const size_t traffic = (size_t)(static_cast<char*>(h->snap) - static_cast<char*>(h->buf)) + out_bytes;
+  return h->nodes >= xcd_range_nodes(h->prec) && traffic <= 230'000'000 ? kXcdRanges : 0;
+}
+
 extern "C" lbm_status lbm_fields(lbm_lattice* h, double* rho, double* ux, double* uy, double* uz, double* T) {
   if (!h) return fail(LBM_ERR_INVALID_ARG, "lattice is NULL");
   if (h->energy) return fail(LBM_ERR_UNSUPPORTED, "lbm_fields (use lbm_enthalpy_fields) is not available for enthalpy lattices");
@@ -1150,6 +1162,7 @@ extern "C" lbm_status lbm_fields(lbm_lattice* h, double* rho, double* ux, double
   if (st != LBM_OK) return st;
   double* d[5];
   for (int i = 0; i < 5; ++i) d[i] = static_cast<double*>(io.dev[i]);
+  const int order = query_order(h, (5 - std::count(ptrs, ptrs + 5, nullptr)) * fb);
   with_types(h, [&](auto lat, auto s_t, auto c_t, const auto& kp) {
     using Lat = decltype(lat);
     using S = decltype(s_t);
@@ -1157,10 +1170,10 @@ extern "C" lbm_status lbm_fields(lbm_lattice* h, double* rho, double* ux, double
     const S st_ = make_store<S>(h);
     if (h->parity)
       hipLaunchKernelGGL((k_fields<Lat, S, C, true>), dim3(h->nblocks), dim3(h->block), 0, h->stream, kp, st_, 0,
-                         h->nodes, d[0], d[1], d[2], d[3], d[4], h->nxcd);
+                         h->nodes, d[0], d[1], d[2], d[3], d[4], order);
     else
       hipLaunchKernelGGL((k_fields<Lat, S, C, false>), dim3(h->nblocks), dim3(h->block), 0, h->stream, kp, st_, 0,
-                         h->nodes, d[0], d[1], d[2], d[3], d[4], h->nxcd);
+                         h->nodes, d[0], d[1], d[2], d[3], d[4], order);
   });
   st = launch_check("fields");
   if (st != LBM_OK) return st;
@@ -1225,6 +1238,7 @@ extern "C" lbm_status lbm_fields_noalloc(lbm_lattice* h, double* rho, double* ux
   // nodes per pass: every host field's slice of the pass fits the array
   const int chunk = nhost > 0 ? (int)std::min<size_t>((size_t)h->nodes, kScratchBytes / (sizeof(double) * nhost))
                               : h->nodes;
+  const int order = query_order(h, (5 - std::count(user, user + 5, nullptr)) * h->nodes * sizeof(double));
   for (int n0 = 0; n0 < h->nodes; n0 += chunk) {
     const int cnt = std::min(chunk, h->nodes - n0);
     double* d[5];
@@ -1242,10 +1256,10 @@ extern "C" lbm_status lbm_fields_noalloc(lbm_lattice* h, double* rho, double* ux
       const S st_ = make_store<S>(h);
       if (h->parity)
         hipLaunchKernelGGL((k_fields<Lat, S, C, true>), grid, dim3(h->block), 0, h->stream, kp, st_, n0, cnt, d[0],
-                           d[1], d[2], d[3], d[4], h->nxcd);
+                           d[1], d[2], d[3], d[4], order);
       else
         hipLaunchKernelGGL((k_fields<Lat, S, C, false>), grid, dim3(h->block), 0, h->stream, kp, st_, n0, cnt, d[0],
-                           d[1], d[2], d[3], d[4], h->nxcd);
+                           d[1], d[2], d[3], d[4], order);
     });
     lbm_status st = launch_check("fields_noalloc");
     if (st != LBM_OK) return st;
@@ -1334,15 +1348,16 @@ extern "C" lbm_status lbm_residual(lbm_lattice* h, double* r, int64_t* at_step) 
 extern "C" lbm_status lbm_totals(lbm_lattice* h, double* mass, double* heat) {
   if (!h) return fail(LBM_ERR_INVALID_ARG, "lattice is NULL");
   if (h->energy) return fail(LBM_ERR_UNSUPPORTED, "lbm_totals is not available for enthalpy lattices");
+  const int order = query_order(h, 0);
   with_types(h, [&](auto lat, auto s_t, auto c_t, const auto& kp) {
     using Lat = decltype(lat);
     using S = decltype(s_t);
     using C = decltype(c_t);
     const S st_ = make_store<S>(h);
     if (h->parity)
-      hipLaunchKernelGGL((k_totals<Lat, S, C, true>), dim3(h->nblocks), dim3(h->block), 0, h->stream, kp, st_, h->part, h->nxcd);
+      hipLaunchKernelGGL((k_totals<Lat, S, C, true>), dim3(h->nblocks), dim3(h->block), 0, h->stream, kp, st_, h->part, order);
     else
-      hipLaunchKernelGGL((k_totals<Lat, S, C, false>), dim3(h->nblocks), dim3(h->block), 0, h->stream, kp, st_, h->part, h->nxcd);
+      hipLaunchKernelGGL((k_totals<Lat, S, C, false>), dim3(h->nblocks), dim3(h->block), 0, h->stream, kp, st_, h->part, order);
   });
   lbm_status ls = launch_check("totals");
   if (ls != LBM_OK) return ls;
@@ -1368,9 +1383,6 @@ extern "C" lbm_status lbm_get_state(lbm_lattice* h, double* f, double* g) {
   if (st != LBM_OK) return st;
   double* df = static_cast<double*>(io.dev[0]);
   double* dg = static_cast<double*>(io.dev[1]);
-  // the steps' tile order pays here too, but for FP32, whose FP64 output is most
-  // of the traffic (103^3: FP64 97 -> 88 us, FP16 125^3 115.6 -> 113, FP32 64.8 -> 66.4)
-  const int order = h->prec == LBM_FP32 ? 0 : h->nxcd;
   if (h->energy) {
     if (!g) return LBM_OK;
     if (h->prec == LBM_FP64) {
@@ -1389,9 +1401,9 @@ extern "C" lbm_status lbm_get_state(lbm_lattice* h, double* f, double* g) {
       using C = decltype(c_t);
       const S st_ = make_store<S>(h);
       if (h->parity)
-        hipLaunchKernelGGL((k_get_state<Lat, S, C, true>), dim3(h->nblocks), dim3(h->block), 0, h->stream, kp, st_, df, dg, order);
+        hipLaunchKernelGGL((k_get_state<Lat, S, C, true>), dim3(h->nblocks), dim3(h->block), 0, h->stream, kp, st_, df, dg);
       else
-        hipLaunchKernelGGL((k_get_state<Lat, S, C, false>), dim3(h->nblocks), dim3(h->block), 0, h->stream, kp, st_, df, dg, order);
+        hipLaunchKernelGGL((k_get_state<Lat, S, C, false>), dim3(h->nblocks), dim3(h->block), 0, h->stream, kp, st_, df, dg);
     });
   }
   st = launch_check("get_state");

@@ -23,7 +23,7 @@ std::map<const void*, std::string>& names() {
 }
 std::map<char*, size_t> g_device;         // device allocations
 std::vector<std::string> g_launched;      // kernels of passes and checks, in order
-int g_order = 0;                          // the tile order that the last step was launched with
+int g_order = 0;                          // the tile order of the last step, field or totals launch
 int g_fail_at = -1;                       // the launch of these that fails
 hipError_t g_error = hipSuccess;          // what hipGetLastError returns next
 uint32_t* g_home = nullptr;   // first word of the populations that the first pass read
@@ -77,6 +77,8 @@ hipError_t hipLaunchKernel(const void* fn, dim3, dim3, void** args, size_t, hipS
   } else if (has(name, "k_step")) {
     g_launched.push_back("step");
     if (!has(name, "enthalpy")) g_order = *static_cast<int*>(args[3]);
+  } else if (has(name, "k_fields") || has(name, "k_totals")) {
+    g_order = *static_cast<int*>(args[has(name, "k_fields") ? 9 : 3]);
   }
   if (brick || melt) {
     const Regions src = *static_cast<Regions*>(args[brick ? 1 : 2]), dst = *static_cast<Regions*>(args[brick ? 2 : 3]);
@@ -281,6 +283,27 @@ void step_order() {
   }
 }
 
+// Tile order of queries: by the state and the outputs of the call together.
+void query_order() {
+  const struct { Box box; int all, one, totals; } cases[] = {
+      {{{103, 103, 103}, 19, LBM_FP32, false}, 8, 8, 8},         {{{103, 103, 103}, 19, LBM_FP64, false}, 0, 0, 8},
+      {{{125, 125, 125}, 19, LBM_FP16_STORAGE, true}, 8, 8, 8},  {{{126, 126, 126}, 19, LBM_FP32, false}, 0, 8, 8},
+      {{{140, 140, 140}, 15, LBM_FP32, false}, 0, 0, 0},         {{{64, 64, 64}, 15, LBM_FP32, false}, 0, 0, 0},
+  };
+  for (const auto& c : cases) {
+    Run r(box_params(c.box));
+    const int* d = c.box.dim;
+    void* out = nullptr;
+    (void)hipMalloc(&out, (size_t)d[0] * d[1] * d[2] * 8);
+    double* const o = static_cast<double*>(out);
+    CHECK(lbm_fields(r.h, o, o, o, o, o) == LBM_OK && g_order == c.all, "fields %d^3: %d", d[0], g_order);
+    CHECK(lbm_fields(r.h, 0, 0, 0, 0, o) == LBM_OK && g_order == c.one, "T %d^3: %d", d[0], g_order);
+    CHECK(lbm_fields_noalloc(r.h, 0, 0, 0, 0, o) == LBM_OK && g_order == c.one, "T %d^3: %d", d[0], g_order);
+    CHECK(lbm_totals(r.h, nullptr, nullptr) == LBM_OK && g_order == c.totals, "totals %d^3: %d", d[0], g_order);
+    (void)hipFree(out);
+  }
+}
+
 // Marching passes: not where a row fills few lanes or a block few rows, where they
 // took up to 20 times the single steps.
 void marching() {
@@ -300,7 +323,7 @@ void marching() {
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> scenarios = {{"capture", capture}, {"offered", offered}, {"failed", failed}, {"marching", marching},
-                                                         {"step_order", step_order}};
+                                                         {"step_order", step_order}, {"query_order", query_order}};
   const auto it = argc == 2 ? scenarios.find(argv[1]) : scenarios.end();
   if (it == scenarios.end()) return 2;
   it->second();

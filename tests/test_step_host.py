@@ -21,7 +21,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["capture", "offered", "failed", "marching", "step_order"])
+@pytest.mark.parametrize("scenario", ["capture", "offered", "failed", "marching", "step_order", "query_order"])
 def test_host_side_of_passes(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr

@@ -940,6 +940,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_totals(const KParams<C> kp, const
 // with the wall.  (At Ra = 1e6 the flux per node is about 1/700 of a
 // population, and the FP32 rounding of the wall term alone would move Nu by
 // 4e-5.)
+constexpr int kWallChunks = 64;  // gridDim.x at most
 template <class Lat, class S, class C, bool ODD>
 __global__ void __launch_bounds__(kMaxBlock) k_wall_flux(const KParams<C> kp, const S state,
                                                          const int* __restrict__ isothermal, double* part,
@@ -974,10 +975,18 @@ __global__ void __launch_bounds__(kMaxBlock) k_wall_flux(const KParams<C> kp, co
   block_reduce<1>(v, 0u);
   const int chunks = (int)gridDim.x;
   if (threadIdx.x == 0) st_agent(part + face * chunks + (int)blockIdx.x, v[0]);
-  if (!last_block(done, gridDim.x * gridDim.y) || threadIdx.x >= 6) return;
+  if (!last_block(done, gridDim.x * gridDim.y)) return;
+  // all chunk sums are fetched at once: a thread per face that fetched its own one after
+  // another took 9 of the 30 us of a query with 64 chunks (256^3 FP64; 26 us with a
+  // second launch for this)
+  __shared__ double sums[6 * kWallChunks];
+  for (int i = (int)threadIdx.x; i < 6 * chunks; i += (int)blockDim.x) sums[i] = ld_agent(part + i);
+  __syncthreads();
+  if (threadIdx.x >= 6) return;
   const int f = (int)threadIdx.x;
   double s = 0.0;
-  for (int b = 0; b < chunks; ++b) s += ld_agent(part + f * chunks + b);
+#pragma unroll 8
+  for (int b = 0; b < chunks; ++b) s += sums[f * chunks + b];
   out[f] = host[f] = s;
 }
 

@@ -1284,7 +1284,7 @@ static lbm_status nusselt_enqueue(lbm_lattice* h) {
   const int dims[3] = {h->p.nx, h->p.ny, h->p.nz};
   int face_max = 1;
   for (int a = 0; a < 3; ++a) face_max = std::max(face_max, dims[(a + 1) % 3] * dims[(a + 2) % 3]);
-  const int chunks = std::max(1, std::min(64, face_max / 1024));
+  const int chunks = std::max(1, std::min(kWallChunks, face_max / 1024));
   with_types(h, [&](auto lat, auto s_t, auto c_t, const auto& kp) {
     using Lat = decltype(lat);
     using S = decltype(s_t);

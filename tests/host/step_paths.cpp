@@ -2,7 +2,8 @@
 // functions that liblbm.so calls (an executable's definitions come before those
 // of the runtime library).  Device memory is host memory and launches are recorded
 // instead of run; a pass of several steps counts itself up in the first word of
-// the populations it writes.  One scenario per call, named in argv[1].
+// the populations it writes.  One scenario per call, named in argv[1]; or "kernel" and a
+// box, for the kernel that its passes take.
 #include <hip/hip_runtime_api.h>
 
 #include <cstdio>
@@ -323,6 +324,15 @@ void marching() {
 }  // namespace
 
 int main(int argc, char** argv) {
+  if (argc == 7 && std::string(argv[1]) == "kernel") {  // table precision nx ny nz
+    const int prec = std::atoi(argv[3]), dim[3] = {std::atoi(argv[4]), std::atoi(argv[5]), std::atoi(argv[6])};
+    const std::string table = argv[2];
+    const int kernel = table == "FLOW"   ? lbm::brick_shape(dim, prec, 256).threads
+                       : table == "MELT" ? lbm::brick_shape_enthalpy(dim, prec, 256).threads
+                                         : lbm::march_variant(dim, prec, 256);
+    std::printf("%d\n", kernel);
+    return 0;
+  }
   const std::map<std::string, void (*)()> scenarios = {{"capture", capture}, {"offered", offered}, {"failed", failed}, {"marching", marching},
                                                          {"step_order", step_order}, {"query_order", query_order}};
   const auto it = argc == 2 ? scenarios.find(argv[1]) : scenarios.end();

@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+import pass_shapes
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = os.path.join(ROOT, "tests", "host", "step_paths.cpp")
 LIB_DIR = os.path.join(ROOT, "paper_1611_03329_amd")
@@ -25,3 +27,13 @@ def program(tmp_path_factory):
 def test_host_side_of_passes(program, scenario):
     r = subprocess.run([program, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("table", ["FLOW", "MELT", "MARCH"])
+def test_the_boxes_of_the_gpu_tests_reach_their_kernels(program, table):
+    for name, row in getattr(pass_shapes, table).items():
+        shape, kernels = row[0], row[-1]
+        for prec, want in kernels.items():
+            args = ["kernel", table, str(["fp64", "fp32", "fp16"].index(prec)), *map(str, shape)]
+            got = subprocess.run([program, *args], capture_output=True, text=True, timeout=60, check=True).stdout
+            assert int(got) == want, (table, name, prec)

@@ -103,14 +103,14 @@ struct Store {
 constexpr int kTileShift = 11;
 constexpr uint32_t kTile = 1u << kTileShift;
 template <uint32_t P>
-__device__ __forceinline__ uint32_t tiled(uint32_t pop, uint32_t n) {
+__host__ __device__ __forceinline__ uint32_t tiled(uint32_t pop, uint32_t n) {
   return (((n >> kTileShift) * P + pop) << kTileShift) | (n & (kTile - 1u));
 }
 // element of moving flow population i >= 1 and moving temperature population
 // k >= 1 of node n
 template <class Lat>
-__device__ __forceinline__ uint32_t fslot(int i, uint32_t n) { return tiled<(uint32_t)(Lat::Q - 1)>((uint32_t)(i - 1), n); }
-__device__ __forceinline__ uint32_t gslot(int k, uint32_t n) { return tiled<6u>((uint32_t)(k - 1), n); }
+__host__ __device__ __forceinline__ uint32_t fslot(int i, uint32_t n) { return tiled<(uint32_t)(Lat::Q - 1)>((uint32_t)(i - 1), n); }
+__host__ __device__ __forceinline__ uint32_t gslot(int k, uint32_t n) { return tiled<6u>((uint32_t)(k - 1), n); }
 // The rest populations f_0 and g_0 share the rest region, tiled in pairs,
 // unless the flow populations are FP16 (f_0 in r0, g_0 alone in the rest region).
 template <class S>
@@ -229,7 +229,7 @@ struct Nbr {
 };
 
 template <class C>
-__device__ __forceinline__ Nbr make_nbr(const KParams<C>& kp, int x, int y, int z) {
+__host__ __device__ __forceinline__ Nbr make_nbr(const KParams<C>& kp, int x, int y, int z) {
   Nbr b;
   const int c[3] = {x, y, z};
   const int dim[3] = {kp.nx, kp.ny, kp.nz};
@@ -248,7 +248,7 @@ __device__ __forceinline__ Nbr make_nbr(const KParams<C>& kp, int x, int y, int 
 // Link along velocity e taken with sign SG (+1: to x + e, -1: to x - e):
 // node offset and whether the linked node exists.
 template <int EX, int EY, int EZ, int SG>
-__device__ __forceinline__ void link(const Nbr& b, int& off, bool& in) {
+__host__ __device__ __forceinline__ void link(const Nbr& b, int& off, bool& in) {
   off = 0;
   in = true;
   if constexpr (EX != 0) {
@@ -284,7 +284,7 @@ __device__ __forceinline__ void link(const Nbr& b, int& off, bool& in) {
 // 512x128x128 FP32 1.5 %) and keep link and fslot; two-step passes (k_brick2), which one wavefront's serial
 // instructions bound, take it in every precision (32^3 FP64 598 -> 575 us per 100 steps).
 template <uint32_t P, class L, int I, int SG, class T>
-__device__ __forceinline__ uint32_t link_at(const Nbr& b, int n, uint32_t own, bool& in) {
+__host__ __device__ __forceinline__ uint32_t link_at(const Nbr& b, int n, uint32_t own, bool& in) {
   constexpr uint32_t sz = sizeof(T), tile = kTile * sz;
   constexpr int io = L::opp(I), there = SG < 0 ? io : I, here = SG < 0 ? I : io;
   constexpr uint32_t apart = (uint32_t)(I < io ? io - I : I - io) * tile;
@@ -301,7 +301,7 @@ __device__ __forceinline__ uint32_t link_at(const Nbr& b, int n, uint32_t own, b
   return in ? at : own + (here > there ? apart : 0u);
 }
 template <class L, int I, class T>
-__device__ __forceinline__ LBM_GLOBAL char* link_base(T* region) {
+__host__ __device__ __forceinline__ LBM_GLOBAL char* link_base(T* region) {
   constexpr int io = L::opp(I), lo = I < io ? I : io;
   return (LBM_GLOBAL char*)region + (size_t)(lo - 1) * kTile * sizeof(T);
 }

@@ -1,6 +1,7 @@
-"""Lattice.set_state and its caller's tensors: they have been read when it
-returns, whichever stream the lattice runs on and whichever stream they are
-freed to or written from next."""
+"""Lattice.set_state and its caller's tensors: what the caller's stream still has to
+write into them comes first, and they have been read when it returns, whichever
+stream the lattice runs on and whichever stream they are freed to or written from
+next."""
 import types
 
 import numpy as np
@@ -29,11 +30,12 @@ def test_the_inputs_have_been_read_on_return(monkeypatch, own):
 
     lat = object.__new__(Lattice)
     lat.stream, lat.device, lat.shape, lat.q, lat._h = Stream(), torch.device("cpu"), (2, 3, 4), 15, None
+    lat.buf = torch.empty(0)
     monkeypatch.setattr(torch.cuda, "current_stream",
                         lambda device=None: lat.stream if own else types.SimpleNamespace(cuda_stream=32))
     monkeypatch.setattr(lbm, "_lib", types.SimpleNamespace(lbm_set_state=lambda *a: calls.append("copy") or 0))
     lat.set_state(np.zeros((15, 2, 3, 4)), np.zeros((7, 2, 3, 4)))
-    assert calls[-2:] == ["copy", "wait"]
+    assert calls == ([] if own else ["order"]) + ["copy", "wait"]
 
 
 @pytest.mark.gpu
@@ -61,3 +63,22 @@ def test_inputs_of_another_stream_may_change_on_return():
                 df.copy_(f)
                 dg.copy_(g)
             side.synchronize()
+
+
+@pytest.mark.gpu
+def test_inputs_still_being_written_come_first():
+    if not torch.cuda.is_available():  # pragma: no cover - CPU container
+        pytest.skip("no GPU")
+    print("case set_state after work of the caller's stream", flush=True)
+    with Lattice(lbm_inputs.periodic_box((48, 40, 32)), "fp64", stream=torch.cuda.Stream()) as lat:
+        f, g = (torch.from_numpy(a).cuda() for a in lbm_inputs.random_state(19, lat.shape, 3, amp=0.05))
+        df, dg = torch.zeros_like(f), torch.zeros_like(g)
+        x = torch.ones(4096, 4096, device="cuda")
+        torch.cuda.synchronize()
+        for _ in range(40):  # work that the copies below wait for
+            x = x @ x * 1e-4
+        df.copy_(f)
+        dg.copy_(g)
+        lat.set_state(df, dg)
+        got = lat.get_state()
+        assert all(float((a - b).abs().max()) <= 2.0 ** -51 for a, b in zip(got, (f, g)))

@@ -728,9 +728,12 @@ __device__ __forceinline__ void step_block(const KParams<C>& kp, const S& state,
   }
 }
 
-// Partial results that another block of the same launch reads go past the XCD's
-// L2 (agent scope, which the L2 caches of the XCDs share no lines for).  A fence
-// instead would write back a whole L2 per block: with 100 blocks it took 10 us.
+// Partial results that another block of the same launch reads.  A fence, or release
+// and acquire on the counter below, would write back and invalidate a whole L2 per
+// block: with 100 blocks that took 10 us.  Relaxed accesses at agent scope order
+// nothing in the language; what the reductions rest on instead is a property of gfx950
+// (as of gfx942): an agent-scope store writes through the XCD's L2 and counts in vmcnt
+// until it is performed at the memory the XCDs share, and an agent-scope load reads there.
 __device__ __forceinline__ void st_agent(double* p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -744,7 +747,7 @@ __device__ __forceinline__ double ld_agent(const double* p) {
 __device__ __forceinline__ bool last_block(uint32_t* count, uint32_t total) {
   __shared__ int last;
   if (threadIdx.x == 0) {
-    // the stores are complete at agent scope once they are counted down
+    // vmcnt 0: this thread's agent-scope stores have been performed (see st_agent)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     last = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1;
     if (last) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

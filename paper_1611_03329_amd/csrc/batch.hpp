@@ -53,7 +53,7 @@ __device__ __forceinline__ int member_of(const M* __restrict__ mem, int nmem, in
 // gridDim.x, ...  A grid smaller than the tile count
 // keeps its blocks resident and lets them walk several tiles (a persistent
 // launch).  With nxcd > 1 the grid is a multiple of nxcd.
-template <class Lat, class S, class C, bool ODD, int MODE, bool GEN, bool BYTES>
+template <class Lat, class S, class C, bool ODD, int MODE, bool GEN>
 __device__ __forceinline__ void step_tiles(const Member<S, C>* __restrict__ mem, int nmem, int ntiles, int nxcd) {
   int t, end, stride;
   if (nxcd < 0) {
@@ -92,17 +92,17 @@ __device__ __forceinline__ void step_tiles(const Member<S, C>* __restrict__ mem,
     if (lb == 0 && threadIdx.x == 0) gbl(clk)[ODD ? 0 : 1] = now + 1u;
     if constexpr (MODE == kModeCompare) {
       // a member that joined after the last snapshot has nothing to compare yet
-      if (mem[m].check) step_block<Lat, S, C, ODD, kModeCompare, GEN, BYTES>(kp, sto, snap, part, lb, seed);
-      else step_block<Lat, S, C, ODD, kModePlain, GEN, BYTES>(kp, sto, snap, part, lb, seed);
+      if (mem[m].check) step_block<Lat, S, C, ODD, kModeCompare, GEN>(kp, sto, snap, part, lb, seed);
+      else step_block<Lat, S, C, ODD, kModePlain, GEN>(kp, sto, snap, part, lb, seed);
       // the block reduction's shared slots are reused by the next tile
       __syncthreads();
     } else if constexpr (MODE == kModeSpan) {
       // without a snapshot yet the member only takes one
-      if (mem[m].check) step_block<Lat, S, C, ODD, kModeSpan, GEN, BYTES>(kp, sto, snap, part, lb, seed);
-      else step_block<Lat, S, C, ODD, kModeSnapshot, GEN, BYTES>(kp, sto, snap, part, lb, seed);
+      if (mem[m].check) step_block<Lat, S, C, ODD, kModeSpan, GEN>(kp, sto, snap, part, lb, seed);
+      else step_block<Lat, S, C, ODD, kModeSnapshot, GEN>(kp, sto, snap, part, lb, seed);
       __syncthreads();
     } else {
-      step_block<Lat, S, C, ODD, MODE, GEN, BYTES>(kp, sto, snap, part, lb, seed);
+      step_block<Lat, S, C, ODD, MODE, GEN>(kp, sto, snap, part, lb, seed);
     }
   }
 }
@@ -112,32 +112,22 @@ __device__ __forceinline__ void step_tiles(const Member<S, C>* __restrict__ mem,
 // to 157 and, sharing the kernel with the lean rules, cut every wavefront's
 // occupancy to 3 (the channel ran 12-18 % slower).  With FP64 arithmetic the
 // same limit would spill heavily, so that kernel keeps its own budget.
-//
-// BYTES: see link_at.  The D3Q19 odd step of FP16 storage with the general rules
-// spills 18 registers with byte offsets in both gather and scatter (76 B of
-// scratch) and none with element indices in gather; a small box, bound by one
-// wavefront's serial work, pays for the spills, a larger one gains more from the
-// fewer instructions.  Measured (us per step, BYTES / not): 20^3 6.00 / 5.53,
-// 32^3 6.59 / 6.12, 48^3 9.56 / 9.16, 64^3 14.04 / 13.97, 64x96x80 16.6 / 17.2,
-// 125^3 43.5 / 45.4, 256x256x128 187 / 191: single lattices of up to kSpillNodes nodes
-// take element indices.
-constexpr int kSpillNodes = 1 << 18;
-template <class Lat, class S, class C, bool ODD, int MODE, bool GEN, bool BYTES>
+template <class Lat, class S, class C, bool ODD, int MODE, bool GEN>
 __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(4, 8)))
 k_step(const Member<S, C>* __restrict__ mem, int nmem, int ntiles, int nxcd) {
-  step_tiles<Lat, S, C, ODD, MODE, GEN, BYTES>(mem, nmem, ntiles, nxcd);
+  step_tiles<Lat, S, C, ODD, MODE, GEN>(mem, nmem, ntiles, nxcd);
 }
 template <class Lat, class S, class C, bool ODD, int MODE, bool GEN>
 __global__ void __launch_bounds__(kMaxBlock) k_step_fp64(const Member<S, C>* __restrict__ mem, int nmem,
                                                          int ntiles, int nxcd) {
-  step_tiles<Lat, S, C, ODD, MODE, GEN, false>(mem, nmem, ntiles, nxcd);
+  step_tiles<Lat, S, C, ODD, MODE, GEN>(mem, nmem, ntiles, nxcd);
 }
 
 // The step kernel for arithmetic type C.
-template <class Lat, class S, class C, bool ODD, int MODE, bool GEN, bool BYTES = kStochastic<S>>
+template <class Lat, class S, class C, bool ODD, int MODE, bool GEN>
 constexpr auto step_kernel() {
   if constexpr (std::is_same<C, double>::value) return &k_step_fp64<Lat, S, C, ODD, MODE, GEN>;
-  else return &k_step<Lat, S, C, ODD, MODE, GEN, BYTES>;
+  else return &k_step<Lat, S, C, ODD, MODE, GEN>;
 }
 
 // Block m folds member m's partials of the last compare step and forms its

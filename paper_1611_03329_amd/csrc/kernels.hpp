@@ -651,9 +651,9 @@ __device__ __forceinline__ void residual_terms(const KParams<C>& kp, C cx, C cy,
 //   MODE 3 does both: it compares with the snapshot, then replaces it.
 // The per-node body of a step: gather, moments, residual bookkeeping,
 // collisions, scatter.  G selects the general wall rules; seed (a hash of the
-// lattice's step count) drives the stochastic rounding of FP16 storage; BYTES:
-// gather takes its links from byte offsets (scatter does wherever storage is FP16).
-template <class Lat, class S, class C, bool ODD, int MODE, bool G, bool BYTES>
+// lattice's step count) drives the stochastic rounding of FP16 storage; GEN: the
+// kernel holds the general rules.
+template <class Lat, class S, class C, bool ODD, int MODE, bool G, bool GEN>
 __device__ __forceinline__ void step_node(const KParams<C>& kp, const S& state, C* __restrict__ snap, int n,
                                           const Nbr& nb, double (&red)[5], uint32_t seed) {
   C h[Lat::Q], p[7];
@@ -664,8 +664,14 @@ __device__ __forceinline__ void step_node(const KParams<C>& kp, const S& state, 
   // step but 1.5 % slower in the odd step, whose loads reach neighbour tiles.
   constexpr bool kLoadPriority =
       kStochastic<S> || std::is_same<C, double>::value || (!ODD && std::is_same<C, float>::value);
+  // The D3Q19 odd step with the general rules keeps element indices in its gather: with
+  // byte offsets in scatter too it spills 18 registers (76 B of scratch), with them in
+  // scatter alone none.  Measured (us per step; element indices in both, byte offsets in
+  // both, in scatter alone): channels 128x64x64 32.1, 32.9, 30.1, 320x160x160 209, 254,
+  // 206; moving lid 20^3 5.56, 5.91, 5.48, 125^3 49.8, 43.9, 48.5, 256x256x128 200, 188, 193.
+  constexpr bool kGatherBytes = kStochastic<S> && !(GEN && Lat::Q == 19);
   if constexpr (kLoadPriority) __builtin_amdgcn_s_setprio(1);
-  gather<Lat, ODD, G, S, C, true, BYTES>(kp, state, n, nb, h, p);
+  gather<Lat, ODD, G, S, C, true, kGatherBytes>(kp, state, n, nb, h, p);
   if constexpr (kLoadPriority) __builtin_amdgcn_s_setprio(0);
   const Pairs<Lat, C> P = make_pairs<Lat, C>(h);
   const Macro<C> M = macro<Lat, kFlowScale<S>, C>(kp, P, p);
@@ -700,7 +706,7 @@ __device__ __forceinline__ bool on_special_face(const KParams<C>& kp, int x, int
 // With GEN the general wall rules run only in wavefronts that hold a node on a
 // moving or open face; every other wavefront takes the lean rules, which give
 // the same result for its nodes.  The choice is uniform per wavefront.
-template <class Lat, class S, class C, bool ODD, int MODE, bool GEN, bool BYTES>
+template <class Lat, class S, class C, bool ODD, int MODE, bool GEN>
 __device__ __forceinline__ void step_block(const KParams<C>& kp, const S& state, C* __restrict__ snap,
                                            double* __restrict__ part, int lb, uint32_t seed) {
   const int n = lb * blockDim.x + threadIdx.x;
@@ -711,11 +717,11 @@ __device__ __forceinline__ void step_block(const KParams<C>& kp, const S& state,
     const Nbr nb = make_nbr(kp, x, y, z);
     if constexpr (GEN) {
       if (__ballot(on_special_face(kp, x, y, z)) != 0)
-        step_node<Lat, S, C, ODD, MODE, true, BYTES>(kp, state, snap, n, nb, red, seed);
+        step_node<Lat, S, C, ODD, MODE, true, GEN>(kp, state, snap, n, nb, red, seed);
       else
-        step_node<Lat, S, C, ODD, MODE, false, BYTES>(kp, state, snap, n, nb, red, seed);
+        step_node<Lat, S, C, ODD, MODE, false, GEN>(kp, state, snap, n, nb, red, seed);
     } else {
-      step_node<Lat, S, C, ODD, MODE, false, BYTES>(kp, state, snap, n, nb, red, seed);
+      step_node<Lat, S, C, ODD, MODE, false, GEN>(kp, state, snap, n, nb, red, seed);
     }
   }
   if constexpr (MODE == kModeCompare || MODE == kModeSpan) {

@@ -884,7 +884,7 @@ extern "C" lbm_status lbm_derived_params(const lbm_lattice* h, lbm_derived* d) {
 }
 
 // ------------------------------------------------------------------ step
-template <class Lat, class S, class C, bool ODD, bool GEN, bool BYTES = kStochastic<S>>
+template <class Lat, class S, class C, bool ODD, bool GEN>
 static void launch_step_mode(lbm_lattice* h, const KParams<C>& kp, int mode) {
   const auto* mem = static_cast<const Member<S, C>*>(h->dev_member);
   const int run = ODD ? h->odd_run : 0, nx = run > 0 ? -run : h->nxcd;
@@ -895,13 +895,13 @@ static void launch_step_mode(lbm_lattice* h, const KParams<C>& kp, int mode) {
   // 728 against 632 us at 256^3)
   const unsigned lds = ODD ? 0u : (unsigned)h->even_lds;
   if (mode == kModePlain)
-    hipLaunchKernelGGL((step_kernel<Lat, S, C, ODD, kModePlain, GEN, BYTES>()), g, b, lds, h->stream, mem, 1, h->nblocks,
+    hipLaunchKernelGGL((step_kernel<Lat, S, C, ODD, kModePlain, GEN>()), g, b, lds, h->stream, mem, 1, h->nblocks,
                        nx);
   else if (mode == kModeSnapshot)
-    hipLaunchKernelGGL((step_kernel<Lat, S, C, ODD, kModeSnapshot, GEN, BYTES>()), g, b, 0, h->stream, mem, 1,
+    hipLaunchKernelGGL((step_kernel<Lat, S, C, ODD, kModeSnapshot, GEN>()), g, b, 0, h->stream, mem, 1,
                        h->nblocks, nx);
   else
-    hipLaunchKernelGGL((step_kernel<Lat, S, C, ODD, kModeCompare, GEN, BYTES>()), g, b, 0, h->stream, mem, 1,
+    hipLaunchKernelGGL((step_kernel<Lat, S, C, ODD, kModeCompare, GEN>()), g, b, 0, h->stream, mem, 1,
                        h->nblocks, nx);
 }
 
@@ -914,12 +914,6 @@ static void launch_step(lbm_lattice* h, const KParams<C>& kp, int mode) {
     if (gen) launch_step_mode<Lat, S, C, false, true>(h, kp, mode);
     else launch_step_mode<Lat, S, C, false, false>(h, kp, mode);
     return;
-  }
-  if constexpr (kStochastic<S> && Lat::Q == 19) {
-    if (gen && h->nodes <= kSpillNodes) {
-      launch_step_mode<Lat, S, C, true, true, false>(h, kp, mode);
-      return;
-    }
   }
   if (gen) launch_step_mode<Lat, S, C, true, true>(h, kp, mode);
   else launch_step_mode<Lat, S, C, true, false>(h, kp, mode);

@@ -1,7 +1,6 @@
-"""GPU test of the two kernels of the FP16 odd step with the general wall rules on
-D3Q19: a small lattice of its own takes its links' element indices in the gather, a
-batch and larger lattices byte offsets.  Both give the same states, bit for bit, in
-plain and check steps and also at the size where the choice changes."""
+"""GPU test of FP16 storage with a moving lid and an open face on D3Q19, whose odd
+step takes element indices in its gather and byte offsets in its scatter: alone
+and in a batch the states are the same, bit for bit, in plain and check steps."""
 import pytest
 
 import lbm_inputs
@@ -19,7 +18,7 @@ LID = face("wall", "adiabatic", 0.0, (0.02, 0.0, 0.01))
 
 
 @pytest.mark.parametrize("shape", [(20, 13, 11), (5, 1, 3), (64, 64, 64), (65, 64, 64)])
-def test_a_small_lattice_steps_as_in_a_batch(shape):
+def test_a_lattice_steps_as_in_a_batch(shape):
     print(f"case general links {shape}", flush=True)
     wl = lbm_inputs.cavity(shape, rayleigh=1e3, seed=5, s_nu_set=1.2)
     wl["faces"][5] = LID

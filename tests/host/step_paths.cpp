@@ -272,7 +272,7 @@ void step_order() {
   const struct { Box box; int even, odd; } cases[] = {
       {{{103, 103, 103}, 19, LBM_FP32, false}, 8, 8},         {{{125, 125, 125}, 19, LBM_FP16_STORAGE, false}, 8, 8},
       {{{155, 155, 155}, 19, LBM_FP32, false}, 8, 8},         {{{160, 160, 168}, 15, LBM_FP32, false}, 0, 0},
-      {{{128, 128, 100}, 19, LBM_FP16_STORAGE, true}, 0, 0},  {{{165, 165, 165}, 19, LBM_FP16_STORAGE, false}, 0, 0},
+      {{{128, 128, 100}, 19, LBM_FP16_STORAGE, true}, 0, 0},  {{{170, 170, 170}, 19, LBM_FP16_STORAGE, false}, 0, 0},
       {{{128, 128, 100}, 19, LBM_FP32, true}, 8, 8},          {{{64, 64, 64}, 15, LBM_FP64, true}, 0, 0},
       {{{80, 80, 80}, 19, LBM_FP16_STORAGE, false}, 0, 0},    {{{1036, 152, 25}, 19, LBM_FP32, false}, 0, 0},
       {{{168, 168, 168}, 19, LBM_FP32, false}, 0, -32},

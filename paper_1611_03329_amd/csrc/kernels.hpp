@@ -279,7 +279,8 @@ __host__ __device__ __forceinline__ void link(const Nbr& b, int& off, bool& in) 
 // instructions per node instead of 1016 (949 with per-axis deltas on boxes whose tiles
 // hold whole rows, which that replaced) and 102 registers instead of 118; step
 // times 125^3 46.3 -> 43.3 us, 128^3 46.5 -> 45.6, channels 288x96x96 59.8 -> 57.7 and
-// 512x128x128 181 -> 178.6, 64^3 and 256^3 unchanged.  FP32 and FP64 steps, bound
+// 512x128x128 181 -> 178.6, 64^3 and 256^3 unchanged (D3Q19 with the general rules
+// takes them in part, see step_node).  FP32 and FP64 steps, bound
 // by memory traffic, lose with it (103^3 FP32 2.6 %, 192^3 FP64 1.6 %, channel
 // 512x128x128 FP32 1.5 %) and keep link and fslot; two-step passes (k_brick2), which one wavefront's serial
 // instructions bound, take it in every precision (32^3 FP64 598 -> 575 us per 100 steps).

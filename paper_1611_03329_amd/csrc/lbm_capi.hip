@@ -433,13 +433,14 @@ static int even_step_lds(const lbm_params* p, const KParams<C>& k, long long nod
 // them cross that link once instead of twice.  Larger states are bound by DRAM
 // and run faster in hardware order, which keeps all XCDs in one region of
 // memory; so do FP16 steps with moving walls or open faces, which instruction issue
-// bounds, and small boxes, whose steps are latency.  Measured over 2300 boxes
-// (cubes, channels, slabs), time in hardware order over that in ranges, mean by
-// size of state: FP64 60-150 MB 1.02, 150-350 MB 1.05, 350-430 MB 1.02-1.04, above
-// 0.98-1.01; FP32 60-100 MB 1.05, 100-250 MB 1.08, 250-350 MB 1.03-1.06, then D3Q19 1.03 to
-// 400 MB and 0.94-1.02 to 430 MB, D3Q15 1.01 to 370 MB and 0.98 to 430 MB; FP16 60-250 MB 1.06-1.11, 260-300 MB 1.01-1.06, 300-340 MB
-// 0.97-1.03, above 0.97; FP16 channels D3Q19 1.02-0.91, D3Q15 1.00-0.93 with size.  By nodes: FP64 and FP32 2.6e5 to 3e5 0.91-1.10, from 3e5 1.02-1.05; FP16 2.6e5 to
-// 3e5 0.92, from 2^20 1.05.
+// bounds, and small boxes, whose steps are latency.  Measured over 2300 boxes (cubes,
+// channels, slabs), time in hardware order over that in ranges, mean by size of state:
+// FP64 60-150 MB 1.02, 150-350 MB 1.05, 350-430 MB 1.02-1.04, above 0.98-1.01; FP32
+// 60-100 MB 1.05, 100-250 MB 1.08, 250-350 MB 1.03-1.06, then D3Q19 1.03 to 400 MB and
+// 0.94-1.02 to 430 MB, D3Q15 1.01 to 370 MB and 0.98 to 430 MB; FP16 60-250 MB 1.06-1.11,
+// 260-300 MB 1.01-1.06, 300-340 MB 0.97-1.03, above 0.97; FP16 channels D3Q19 1.02-0.91,
+// D3Q15 1.00-0.93 with size.  By nodes: FP64 and FP32 2.6e5 to 3e5 0.91-1.10, from 3e5
+// 1.02-1.05; FP16 2.6e5 to 3e5 0.92, from 2^20 1.05.
 constexpr int kXcdRanges = 8;
 
 static long long xcd_range_nodes(int prec) { return prec == LBM_FP16_STORAGE ? 1LL << 20 : 300'000LL; }

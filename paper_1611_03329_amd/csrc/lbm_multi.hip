@@ -269,7 +269,7 @@ static MarchGrid march_grid(const int dim[3], int row, int rows, int ncu) {
 //
 // A pass pays where its estimate is below that of two single steps.  An item's
 // plane takes the same time however much of its row lies in the box, and less if
-// fewer rows do (the vector units bound it); to that comes the traffic of the state.
+// fewer rows do; to that comes the traffic of the state.
 // Fitted to 170 boxes of 2^18 to 1.7e7 nodes with edges from 1 to 10^5, which it meets to 6 %
 // (rms); of 600 others that it takes, drawn at random, 4 % ran 2 to 9 % slower than single
 // steps.  Measured per step (us, k_step_enthalpy / passes): FP64 128^3 35.1 / 23.4,

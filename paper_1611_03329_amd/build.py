@@ -47,7 +47,7 @@ def build(extra_flags=(), verbose: bool = False) -> str:
         failed = [(job.returncode, cmd) for cmd, job in jobs if job.wait() != 0]
         if failed:
             raise subprocess.CalledProcessError(*failed[0])
-        subprocess.run([hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp], check=True)
+        subprocess.run([hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *extra_flags, *objs, "-o", tmp], check=True)
     os.replace(tmp, LIB)
     return LIB
 

@@ -390,9 +390,10 @@ class Lattice:
         g = arr(g, 7)
         if f is not None:
             f = arr(f, self.q)
-        # what the caller's stream still has to write into the inputs comes first
+        # what the caller's stream still has to write into the inputs comes first (a
+        # capture on it writes nothing now, and must not take this stream in)
         current = torch.cuda.current_stream(self.buf.device)
-        if self.stream.cuda_stream != current.cuda_stream:
+        if self.stream.cuda_stream != current.cuda_stream and not torch.cuda.is_current_stream_capturing():
             self.stream.wait_stream(current)
         _check(_lib.lbm_set_state(self._h, _ptr(f), _ptr(g)))
         # the copy kernel has read the inputs when this returns, on whichever

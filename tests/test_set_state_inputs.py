@@ -13,8 +13,8 @@ from paper_1611_03329_amd import Lattice, lbm
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("own", [True, False])
-def test_the_inputs_have_been_read_on_return(monkeypatch, own):
+@pytest.mark.parametrize("own, capturing", [(True, False), (False, False), (False, True)])
+def test_the_inputs_have_been_read_on_return(monkeypatch, own, capturing):
     """On the caller's own stream too: a tensor of another stream may be freed
     to that stream, or refilled there, as soon as the call returns."""
     calls = []
@@ -33,9 +33,10 @@ def test_the_inputs_have_been_read_on_return(monkeypatch, own):
     lat.buf = torch.empty(0)
     monkeypatch.setattr(torch.cuda, "current_stream",
                         lambda device=None: lat.stream if own else types.SimpleNamespace(cuda_stream=32))
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing)
     monkeypatch.setattr(lbm, "_lib", types.SimpleNamespace(lbm_set_state=lambda *a: calls.append("copy") or 0))
     lat.set_state(np.zeros((15, 2, 3, 4)), np.zeros((7, 2, 3, 4)))
-    assert calls == ([] if own else ["order"]) + ["copy", "wait"]
+    assert calls == ([] if own or capturing else ["order"]) + ["copy", "wait"]
 
 
 @pytest.mark.gpu
